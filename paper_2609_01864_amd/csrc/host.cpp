@@ -53,8 +53,8 @@ const void *epoch_bump_kernel();
 const void *flush_kernel();
 const void *fill_kernel();
 const void *copy_kernel();
-const void *encode_kernel(int);
-const void *decode_kernel(int);
+hipError_t launch_encode(int, int64_t, int64_t, const float *, const float *, void *, hipStream_t);
+hipError_t launch_decode(int, int64_t, int64_t, const void *, const float *, float *, hipStream_t);
 const void *mlp_kernel(int);
 const void *probe_kernel(int);
 }  // namespace credit
@@ -2023,20 +2023,14 @@ credit_status_t credit_encode(credit_handle_t h, int64_t M, int64_t N, credit_dt
                               const float *row_scale, void *out, void *stream) {
     if (!h || M < 0 || N <= 0 || (int)dt < 0 || (int)dt > 2 || (M > 0 && (!x || !out))) return CREDIT_ERR_INVALID_ARG;
     if (M == 0) return CREDIT_OK;
-    int64_t total = M * N;
-    int grid = (int)std::min<int64_t>(8192, (total + 255) / 256);
-    void *args[] = {&x, &row_scale, &out, &M, &N};
-    return launch(encode_kernel(dt), grid, 256, 0, (hipStream_t)stream, args) == hipSuccess ? CREDIT_OK : CREDIT_ERR_HIP;
+    return launch_encode(dt, M, N, x, row_scale, out, (hipStream_t)stream) == hipSuccess ? CREDIT_OK : CREDIT_ERR_HIP;
 }
 
 credit_status_t credit_decode(credit_handle_t h, int64_t M, int64_t N, credit_dtype_t dt, const void *in,
                               const float *row_scale, float *out, void *stream) {
     if (!h || M < 0 || N <= 0 || (int)dt < 0 || (int)dt > 2 || (M > 0 && (!in || !out))) return CREDIT_ERR_INVALID_ARG;
     if (M == 0) return CREDIT_OK;
-    int64_t total = M * N;
-    int grid = (int)std::min<int64_t>(8192, (total + 255) / 256);
-    void *args[] = {&in, &row_scale, &out, &M, &N};
-    return launch(decode_kernel(dt), grid, 256, 0, (hipStream_t)stream, args) == hipSuccess ? CREDIT_OK : CREDIT_ERR_HIP;
+    return launch_decode(dt, M, N, in, row_scale, out, (hipStream_t)stream) == hipSuccess ? CREDIT_OK : CREDIT_ERR_HIP;
 }
 
 credit_status_t credit_check_errors(credit_handle_t h, void *stream) {

@@ -1,6 +1,6 @@
 // misc.hip -- support kernels: dgamma/dbeta column reductions, the work-free
-// control kernel of the profitability model, cache flush, deterministic fill,
-// the copy-bandwidth probe and the elementwise codecs.
+// control kernel of the profitability model, cache flush, deterministic fill
+// and the copy-bandwidth probe.
 #include "resident.h"
 #include "twopass.h"
 
@@ -146,50 +146,5 @@ __global__ __launch_bounds__(256) void k_copy(const u32x4 *__restrict__ src, u32
     if (i < n) __builtin_nontemporal_store(__builtin_nontemporal_load(src + i), dst + i);
 }
 const void *copy_kernel() { return (const void *)&k_copy; }
-
-// Elementwise FP32 -> dtype: code = RNE(x / scale[row]) (FP8 saturating).
-template <int DT>
-__global__ __launch_bounds__(256) void k_encode(const float *x, const float *scale, void *out, int64_t M, int64_t N) {
-    constexpr int B = Io<DT>::BYTES;
-    const int64_t total = M * N;
-    for (int64_t i = (int64_t)blockIdx.x * 256 + threadIdx.x; i < total; i += (int64_t)gridDim.x * 256) {
-        float v = x[i];
-        if (scale) v = v / scale[i / N];
-        if constexpr (DT == DT_F32) {
-            ((float *)out)[i] = v;
-        } else if constexpr (DT == DT_BF16) {
-            ((unsigned short *)out)[i] = (unsigned short)bf16_bits(v);
-        } else {
-            int w = __builtin_amdgcn_cvt_pk_fp8_f32(sat448(v), 0.f, 0, false);
-            ((unsigned char *)out)[i] = (unsigned char)(w & 0xff);
-        }
-        (void)B;
-    }
-}
-// Elementwise dtype -> FP32: decode(code) * scale[row].
-template <int DT>
-__global__ __launch_bounds__(256) void k_decode(const void *in, const float *scale, float *out, int64_t M, int64_t N) {
-    const int64_t total = M * N;
-    for (int64_t i = (int64_t)blockIdx.x * 256 + threadIdx.x; i < total; i += (int64_t)gridDim.x * 256) {
-        float v;
-        if constexpr (DT == DT_F32) {
-            v = ((const float *)in)[i];
-        } else if constexpr (DT == DT_BF16) {
-            v = __uint_as_float((unsigned)((const unsigned short *)in)[i] << 16);
-        } else {
-            f32x2 t = __builtin_amdgcn_cvt_pk_f32_fp8((int)((const unsigned char *)in)[i], false);
-            v = t.x;
-        }
-        out[i] = scale ? v * scale[i / N] : v;
-    }
-}
-const void *encode_kernel(int dt) {
-    return dt == DT_F32 ? (const void *)&k_encode<DT_F32>
-         : dt == DT_BF16 ? (const void *)&k_encode<DT_BF16> : (const void *)&k_encode<DT_FP8>;
-}
-const void *decode_kernel(int dt) {
-    return dt == DT_F32 ? (const void *)&k_decode<DT_F32>
-         : dt == DT_BF16 ? (const void *)&k_decode<DT_BF16> : (const void *)&k_decode<DT_FP8>;
-}
 
 }  // namespace credit
