@@ -44,8 +44,7 @@ const void *twopass_kernel_pearson_bwd(int, int);
 const void *twopass_kernel_wvar_bwd(int, int);
 const void *resident_kernel_lnq_fwd(int, int);
 const void *twopass_kernel_lnq_fwd(int, int);
-const void *colreduce_kernel();
-const void *colreduce1_kernel();
+hipError_t launch_colreduce(const float *, int, int, int64_t, float *, float *, hipStream_t);
 const void *colstats_kernel(int, bool);
 const void *control_kernel();
 const void *zero_kernel();
@@ -214,8 +213,7 @@ struct Launch {
     int64_t chunk = 0;
     bool xcd = false;
     int parts = 0, rowblocks = 0;  // dgamma/dbeta partial rows
-    int slices = 0;                // first-level column-reduction slices (0: one level)
-    size_t off_slots = 0, off_colpart = 0, off_stats = 0, off_colsum = 0, ws_bytes = 0;
+    size_t off_slots = 0, off_colpart = 0, off_stats = 0, ws_bytes = 0;
 };
 
 }  // namespace
@@ -302,17 +300,6 @@ int occupancy(credit_handle_t h, const void *fn, int block, size_t shmem) {
     return n;
 }
 
-// The dgamma / dbeta partial rows are summed in two levels when there are
-// many: slices of kColPer partial rows each in parallel, then the slices, so
-// the reduction has parallelism over rows as well as columns (fixed order).
-constexpr int kColPer = 16;
-size_t colsum_layout(Launch &L, int ncp, int64_t N, size_t off) {
-    L.slices = L.parts > 2 * kColPer ? (L.parts + kColPer - 1) / kColPer : 0;
-    if (!L.slices) return off;
-    L.off_colsum = off;
-    return align256(off + (size_t)L.slices * ncp * N * 4);
-}
-
 // Rows per workgroup of a resident / split plan (Launch::rows): the option
 // when set, else the library's rule, from back-to-back timings on MI355X
 // (M = 1024..16384): two rows per workgroup where one exchange round per two
@@ -363,7 +350,6 @@ credit_status_t resolve(credit_handle_t h, int k_op, int dt, int64_t M, int64_t 
             L.parts = L.rowblocks;
             L.off_colpart = off;
             off = align256(off + (size_t)L.rowblocks * ncp * N * 4);
-            off = colsum_layout(L, ncp, N, off);
             L.off_stats = off;
             off = align256(off + (size_t)2 * M * 4);
         }
@@ -433,7 +419,6 @@ credit_status_t resolve(credit_handle_t h, int k_op, int dt, int64_t M, int64_t 
         L.parts = L.groups;
         L.off_colpart = off;
         off = align256(off + (size_t)L.groups * ncp * N * 4);
-        off = colsum_layout(L, ncp, N, off);
     }
     L.ws_bytes = off;
     (void)recompute;
@@ -600,23 +585,7 @@ credit_status_t issue(credit_handle_t h, const OpCall &c, const Launch &L, void 
         if (e != hipSuccess) return CREDIT_ERR_HIP;
     }
     if (ncp && (c.dgamma || c.dbeta)) {
-        const float *part = (const float *)(w + L.off_colpart);
-        int parts = L.parts;
-        int n_cp = ncp;
-        int64_t N = c.N;
-        if (L.slices) {
-            float *tmp = (float *)(w + L.off_colsum);
-            int per = kColPer;
-            void *a1[] = {&part, &parts, &n_cp, &N, &per, &tmp};
-            e = hipLaunchKernel(colreduce1_kernel(), dim3((unsigned)((N + 255) / 256), (unsigned)L.slices), dim3(256),
-                                a1, 0, stream);
-            if (e != hipSuccess) return CREDIT_ERR_HIP;
-            part = tmp;
-            parts = L.slices;
-        }
-        float *o0 = c.dgamma, *o1 = c.dbeta;
-        void *args[] = {&part, &parts, &n_cp, &N, &o0, &o1};
-        e = launch(colreduce_kernel(), (int)((N + 255) / 256), 256, 0, stream, args);
+        e = launch_colreduce((const float *)(w + L.off_colpart), L.parts, ncp, c.N, c.dgamma, c.dbeta, stream);
         if (e != hipSuccess) return CREDIT_ERR_HIP;
     }
     return CREDIT_OK;
