@@ -13,7 +13,19 @@ from . import credit as C
 
 
 def _rows(t):
-    return t.reshape(-1, t.shape[-1])
+    return t if t.dim() == 2 else t.reshape(-1, t.shape[-1])
+
+
+def _as(t, like):
+    """t in the shape of `like` (t itself where it has it already)."""
+    return t if t.shape == like.shape else t.view(like.shape)
+
+
+def _grad_rows(dy, dtype):
+    """The incoming gradient as contiguous rows of the operator's dtype."""
+    if dy.dtype != dtype:
+        dy = dy.to(dtype)
+    return _rows(dy.contiguous())
 
 
 class SoftmaxFn(torch.autograd.Function):
@@ -23,13 +35,13 @@ class SoftmaxFn(torch.autograd.Function):
         y, _ = C.softmax_fwd(x2, p=plan)
         ctx.save_for_backward(y)
         ctx.plan_bwd = None
-        return y.view_as(x)
+        return _as(y, x)
 
     @staticmethod
     def backward(ctx, dy):
         (y,) = ctx.saved_tensors
-        dx, _ = C.softmax_bwd(y, _rows(dy.contiguous().to(y.dtype)), p=ctx.plan_bwd)
-        return dx.view(dy.shape), None
+        dx, _ = C.softmax_bwd(y, _grad_rows(dy, y.dtype), p=ctx.plan_bwd)
+        return _as(dx, dy), None
 
 
 class SoftmaxLogitsFn(torch.autograd.Function):
@@ -41,13 +53,13 @@ class SoftmaxLogitsFn(torch.autograd.Function):
         x2 = _rows(x.contiguous())
         y, _ = C.softmax_fwd(x2, p=plan)
         ctx.save_for_backward(x2)
-        return y.view_as(x)
+        return _as(y, x)
 
     @staticmethod
     def backward(ctx, dy):
         (x2,) = ctx.saved_tensors
-        dx, _ = C.softmax_logits_bwd(x2, _rows(dy.contiguous().to(x2.dtype)))
-        return dx.view(dy.shape), None
+        dx, _ = C.softmax_logits_bwd(x2, _grad_rows(dy, x2.dtype))
+        return _as(dx, dy), None
 
 
 class LayerNormFn(torch.autograd.Function):
@@ -57,15 +69,15 @@ class LayerNormFn(torch.autograd.Function):
         y, _, mean, rstd = C.layernorm_fwd(x2, gamma.contiguous(), beta.contiguous(), eps, p=plan)
         ctx.save_for_backward(x2, gamma, mean, rstd)
         ctx.eps = eps
-        return y.view_as(x)
+        return _as(y, x)
 
     @staticmethod
     def backward(ctx, dy):
         x2, gamma, mean, rstd = ctx.saved_tensors
-        dx, _, dg, db = C.layernorm_bwd(x2, _rows(dy.contiguous().to(x2.dtype)), gamma.contiguous(), mean, rstd,
+        dx, _, dg, db = C.layernorm_bwd(x2, _grad_rows(dy, x2.dtype), gamma.contiguous(), mean, rstd,
                                         ctx.eps, need_dgamma=ctx.needs_input_grad[1],
                                         need_dbeta=ctx.needs_input_grad[2])
-        return dx.view(dy.shape), dg, db, None, None
+        return _as(dx, dy), dg, db, None, None
 
 
 class RMSNormFn(torch.autograd.Function):
@@ -75,14 +87,14 @@ class RMSNormFn(torch.autograd.Function):
         y, _, rstd = C.rmsnorm_fwd(x2, gamma.contiguous(), eps, p=plan)
         ctx.save_for_backward(x2, gamma, rstd)
         ctx.eps = eps
-        return y.view_as(x)
+        return _as(y, x)
 
     @staticmethod
     def backward(ctx, dy):
         x2, gamma, rstd = ctx.saved_tensors
-        dx, _, dg = C.rmsnorm_bwd(x2, _rows(dy.contiguous().to(x2.dtype)), gamma.contiguous(), rstd, ctx.eps,
+        dx, _, dg = C.rmsnorm_bwd(x2, _grad_rows(dy, x2.dtype), gamma.contiguous(), rstd, ctx.eps,
                                   need_dgamma=ctx.needs_input_grad[1])
-        return dx.view(dy.shape), dg, None, None
+        return _as(dx, dy), dg, None, None
 
 
 def softmax(x, plan=None, save: str = "output"):

@@ -275,21 +275,28 @@ def _mlp_arrays(feats, targets=None, mask=None):
     return out
 
 
-def _torch():
-    import torch
+_torch_mod = None
+_io = {}  # torch dtype -> I/O dtype
 
-    return torch
+
+def _torch():
+    global _torch_mod
+    if _torch_mod is None:
+        import torch
+
+        _io.update({torch.float32: F32, torch.bfloat16: BF16, torch.uint8: FP8,
+                    getattr(torch, "float8_e4m3fn", torch.uint8): FP8})
+        _torch_mod = torch
+    return _torch_mod
 
 
 def io_dtype(t) -> int:
-    torch = _torch()
-    if t.dtype == torch.float32:
-        return F32
-    if t.dtype == torch.bfloat16:
-        return BF16
-    if t.dtype in (torch.uint8, getattr(torch, "float8_e4m3fn", torch.uint8)):
-        return FP8
-    raise TypeError(f"unsupported I/O dtype {t.dtype}")
+    if _torch_mod is None:
+        _torch()
+    dt = _io.get(t.dtype)
+    if dt is None:
+        raise TypeError(f"unsupported I/O dtype {t.dtype}")
+    return dt
 
 
 def _ptr(t) -> Optional[int]:
@@ -309,20 +316,23 @@ def _validate(M, N, ref, mats=(), vecs=()):
     on that device with at least the given number of contiguous elements.
     The library sees raw pointers only, so a short vector would be read out
     of bounds on the GPU."""
-    torch = _torch()
+    dev, dtype = ref.device, ref.dtype
     for t, name in mats:
         if t is None:
             continue
-        if tuple(t.shape) != (M, N) or t.dim() != 2 or t.stride(1) != 1:
+        if t.dim() != 2 or tuple(t.shape) != (M, N) or t.stride(1) != 1:
             raise ValueError(f"{name}: expected [{M}, {N}] with unit inner stride, got {tuple(t.shape)}")
-        if t.device != ref.device or t.dtype != ref.dtype:
-            raise ValueError(f"{name}: expected {ref.dtype} on {ref.device}, got {t.dtype} on {t.device}")
+        if t.device != dev or t.dtype != dtype:
+            raise ValueError(f"{name}: expected {dtype} on {dev}, got {t.dtype} on {t.device}")
+    if _torch_mod is None:
+        _torch()
+    f32 = _torch_mod.float32
     for t, n, name in vecs:
         if t is None:
             continue
-        if t.dtype != torch.float32 or t.device != ref.device:
-            raise ValueError(f"{name}: expected float32 on {ref.device}, got {t.dtype} on {t.device}")
-        if t.numel() < n or (t.numel() > 1 and t.dim() == 1 and t.stride(0) != 1) or t.dim() > 1 and not t.is_contiguous():
+        if t.dtype != f32 or t.device != dev:
+            raise ValueError(f"{name}: expected float32 on {dev}, got {t.dtype} on {t.device}")
+        if t.numel() < n or not t.is_contiguous():
             raise ValueError(f"{name}: expected at least {n} contiguous elements, got {tuple(t.shape)}")
 
 
@@ -337,6 +347,9 @@ class Handle:
             check(lib().credit_create(self.device, ctypes.byref(p)), "credit_create")
         self.ptr = p
         self._ws = {}
+        # workspace bytes by (op, direction, dtype, M, N, plan): a function of
+        # the shape and the handle's options only, so set_option clears it
+        self._sizes = {}
         # workspaces replaced by a larger one stay allocated until the handle
         # goes away: a launch recorded into a HIP graph keeps the raw address of
         # the workspace it was captured with, and replaying it must not write
@@ -362,6 +375,7 @@ class Handle:
         check(lib().credit_set_selector(self.ptr, sel), "credit_set_selector")
 
     def set_option(self, opt: int, value: int) -> None:
+        self._sizes.clear()
         check(lib().credit_set_option(self.ptr, opt, int(value)), "credit_set_option")
 
     def load_model(self, path: str) -> int:
@@ -479,10 +493,21 @@ class Handle:
 
     # -- internals
     def _stream(self, stream=None) -> int:
-        torch = _torch()
-        if stream is None:
-            stream = torch.cuda.current_stream(self.device)
+        if stream is None:  # the current stream's handle, without a Stream object around it
+            return _torch_mod._C._cuda_getCurrentRawStream(self.device)
         return stream.cuda_stream if hasattr(stream, "cuda_stream") else int(stream)
+
+    def _call_ws(self, op, direction, dtype, M, N, p, stream):
+        """The stream's workspace, large enough for the call."""
+        key = (op, direction, dtype, M, N, None if p is None else (p.variant, p.k))
+        n = self._sizes.get(key)
+        if n is None:
+            n = self.workspace_size(op, direction, dtype, M, N, p) if M > 0 else 0
+            if len(self._sizes) >= 4096:
+                self._sizes.clear()
+            self._sizes[key] = n
+        ws = self._ws.get(stream)
+        return ws if ws is not None and ws.numel() >= n else self.workspace(n, stream)
 
     def workspace(self, nbytes: int, stream: int):
         """A zero-initialised workspace of at least nbytes for this stream."""
@@ -505,8 +530,7 @@ _handles = {}
 
 def handle(device: Optional[int] = None) -> Handle:
     """The process-wide handle of a device (created on first use)."""
-    torch = _torch()
-    d = torch.cuda.current_device() if device is None else int(device)
+    d = _torch().cuda.current_device() if device is None else int(device)
     h = _handles.get(d)
     if h is None:
         h = Handle(d)
@@ -514,21 +538,17 @@ def handle(device: Optional[int] = None) -> Handle:
     return h
 
 
-def _empty_like_out(x, M, N):
-    torch = _torch()
-    return torch.empty((M, N), dtype=x.dtype, device=x.device)
-
-
-def _launch(h: Handle, fn_name: str, op, direction, dtype, M, N, p, stream, build_args):
-    ws_bytes = h.workspace_size(op, direction, dtype, M, N, p) if M > 0 else 0
-    ws = h.workspace(ws_bytes, stream)
-    args = build_args(ws.data_ptr(), ws.numel())
-    check(getattr(lib(), fn_name)(*args), fn_name)
+def _empty_like_out(x):
+    return _torch_mod.empty_like(x, memory_format=_torch_mod.contiguous_format)
 
 
 def _scale_out(x, M):
-    torch = _torch()
+    torch = _torch_mod
     return torch.empty(M, dtype=torch.float32, device=x.device)
+
+
+def _bref(p):
+    return None if p is None else ctypes.byref(p)
 
 
 def softmax_fwd(x, x_scale=None, p: Optional[Plan] = None, out=None, out_scale=None, h: Optional[Handle] = None):
@@ -536,13 +556,13 @@ def softmax_fwd(x, x_scale=None, p: Optional[Plan] = None, out=None, out_scale=N
     h = h or handle(x.device.index)
     dt = io_dtype(x)
     M, N = x.shape
-    _validate(M, N, x, [(out, "out")], [(x_scale, M, "x_scale"), (out_scale, M, "out_scale")])
-    y = out if out is not None else _empty_like_out(x, M, N)
+    _validate(M, N, x, ((out, "out"),), ((x_scale, M, "x_scale"), (out_scale, M, "out_scale")))
+    y = out if out is not None else _empty_like_out(x)
     ys = out_scale if out_scale is not None else (_scale_out(x, M) if dt == FP8 else None)
     s = h._stream()
-    pp = None if p is None else ctypes.byref(p)
-    _launch(h, "credit_softmax_fwd", SOFTMAX, FWD, dt, M, N, p, s,
-            lambda w, wn: (h.ptr, M, N, dt, _ptr(x), _ld(x), _ptr(x_scale), _ptr(y), _ld(y), _ptr(ys), pp, w, wn, s))
+    w = h._call_ws(SOFTMAX, FWD, dt, M, N, p, s)
+    check(lib().credit_softmax_fwd(h.ptr, M, N, dt, x.data_ptr(), _ld(x), _ptr(x_scale), y.data_ptr(), _ld(y),
+                                   _ptr(ys), _bref(p), w.data_ptr(), w.numel(), s), "credit_softmax_fwd")
     return y, ys
 
 
@@ -551,34 +571,33 @@ def softmax_bwd(y, dy, y_scale=None, dy_scale=None, p: Optional[Plan] = None, ou
     h = h or handle(y.device.index)
     dt = io_dtype(y)
     M, N = y.shape
-    _validate(M, N, y, [(dy, "dy"), (out, "out")], [(y_scale, M, "y_scale"), (dy_scale, M, "dy_scale")])
-    dx = out if out is not None else _empty_like_out(y, M, N)
+    _validate(M, N, y, ((dy, "dy"), (out, "out")), ((y_scale, M, "y_scale"), (dy_scale, M, "dy_scale")))
+    dx = out if out is not None else _empty_like_out(y)
     dxs = _scale_out(y, M) if dt == FP8 else None
     s = h._stream()
-    pp = None if p is None else ctypes.byref(p)
-    _launch(h, "credit_softmax_bwd", SOFTMAX, BWD, dt, M, N, p, s,
-            lambda w, wn: (h.ptr, M, N, dt, _ptr(y), _ld(y), _ptr(y_scale), _ptr(dy), _ld(dy), _ptr(dy_scale),
-                           _ptr(dx), _ld(dx), _ptr(dxs), pp, w, wn, s))
+    w = h._call_ws(SOFTMAX, BWD, dt, M, N, p, s)
+    check(lib().credit_softmax_bwd(h.ptr, M, N, dt, y.data_ptr(), _ld(y), _ptr(y_scale), dy.data_ptr(), _ld(dy),
+                                   _ptr(dy_scale), dx.data_ptr(), _ld(dx), _ptr(dxs), _bref(p), w.data_ptr(),
+                                   w.numel(), s), "credit_softmax_bwd")
     return dx, dxs
 
 
 def layernorm_fwd(x, gamma, beta, eps: float = 1e-5, x_scale=None, p: Optional[Plan] = None, out=None,
                   save_stats: bool = True, h: Optional[Handle] = None):
     """Returns (y, y_scale, mean, rstd)."""
-    torch = _torch()
     h = h or handle(x.device.index)
     dt = io_dtype(x)
     M, N = x.shape
-    _validate(M, N, x, [(out, "out")], [(gamma, N, "gamma"), (beta, N, "beta"), (x_scale, M, "x_scale")])
-    y = out if out is not None else _empty_like_out(x, M, N)
+    _validate(M, N, x, ((out, "out"),), ((gamma, N, "gamma"), (beta, N, "beta"), (x_scale, M, "x_scale")))
+    y = out if out is not None else _empty_like_out(x)
     ys = _scale_out(x, M) if dt == FP8 else None
-    mean = torch.empty(M, dtype=torch.float32, device=x.device) if save_stats else None
-    rstd = torch.empty(M, dtype=torch.float32, device=x.device) if save_stats else None
+    mean = _scale_out(x, M) if save_stats else None
+    rstd = _scale_out(x, M) if save_stats else None
     s = h._stream()
-    pp = None if p is None else ctypes.byref(p)
-    _launch(h, "credit_layernorm_fwd", LAYERNORM, FWD, dt, M, N, p, s,
-            lambda w, wn: (h.ptr, M, N, dt, _ptr(x), _ld(x), _ptr(x_scale), _ptr(gamma), _ptr(beta), float(eps),
-                           _ptr(y), _ld(y), _ptr(ys), _ptr(mean), _ptr(rstd), pp, w, wn, s))
+    w = h._call_ws(LAYERNORM, FWD, dt, M, N, p, s)
+    check(lib().credit_layernorm_fwd(h.ptr, M, N, dt, x.data_ptr(), _ld(x), _ptr(x_scale), _ptr(gamma), _ptr(beta),
+                                     float(eps), y.data_ptr(), _ld(y), _ptr(ys), _ptr(mean), _ptr(rstd), _bref(p),
+                                     w.data_ptr(), w.numel(), s), "credit_layernorm_fwd")
     return y, ys, mean, rstd
 
 
@@ -586,62 +605,58 @@ def layernorm_bwd(x, dy, gamma, mean=None, rstd=None, eps: float = 1e-5, x_scale
                   p: Optional[Plan] = None, need_dgamma: bool = True, need_dbeta: bool = True,
                   h: Optional[Handle] = None):
     """Returns (dx, dx_scale, dgamma, dbeta); mean/rstd None -> recomputed."""
-    torch = _torch()
     h = h or handle(x.device.index)
     dt = io_dtype(x)
     M, N = x.shape
-    _validate(M, N, x, [(dy, "dy")], [(gamma, N, "gamma"), (mean, M, "mean"), (rstd, M, "rstd"),
-                                     (x_scale, M, "x_scale"), (dy_scale, M, "dy_scale")])
-    dx = _empty_like_out(x, M, N)
+    _validate(M, N, x, ((dy, "dy"),), ((gamma, N, "gamma"), (mean, M, "mean"), (rstd, M, "rstd"),
+                                       (x_scale, M, "x_scale"), (dy_scale, M, "dy_scale")))
+    dx = _empty_like_out(x)
     dxs = _scale_out(x, M) if dt == FP8 else None
-    dg = torch.empty(N, dtype=torch.float32, device=x.device) if need_dgamma else None
-    db = torch.empty(N, dtype=torch.float32, device=x.device) if need_dbeta else None
+    dg = _scale_out(x, N) if need_dgamma else None
+    db = _scale_out(x, N) if need_dbeta else None
     s = h._stream()
-    pp = None if p is None else ctypes.byref(p)
-    _launch(h, "credit_layernorm_bwd", LAYERNORM, BWD, dt, M, N, p, s,
-            lambda w, wn: (h.ptr, M, N, dt, _ptr(x), _ld(x), _ptr(x_scale), _ptr(dy), _ld(dy), _ptr(dy_scale),
-                           _ptr(gamma), _ptr(mean), _ptr(rstd), float(eps), _ptr(dx), _ld(dx), _ptr(dxs),
-                           _ptr(dg), _ptr(db), pp, w, wn, s))
+    w = h._call_ws(LAYERNORM, BWD, dt, M, N, p, s)
+    check(lib().credit_layernorm_bwd(h.ptr, M, N, dt, x.data_ptr(), _ld(x), _ptr(x_scale), dy.data_ptr(), _ld(dy),
+                                     _ptr(dy_scale), _ptr(gamma), _ptr(mean), _ptr(rstd), float(eps), dx.data_ptr(),
+                                     _ld(dx), _ptr(dxs), _ptr(dg), _ptr(db), _bref(p), w.data_ptr(), w.numel(), s),
+          "credit_layernorm_bwd")
     return dx, dxs, dg, db
 
 
 def rmsnorm_fwd(x, gamma, eps: float = 1e-5, x_scale=None, p: Optional[Plan] = None, out=None,
                 save_stats: bool = True, h: Optional[Handle] = None):
     """Returns (y, y_scale, rstd)."""
-    torch = _torch()
     h = h or handle(x.device.index)
     dt = io_dtype(x)
     M, N = x.shape
-    _validate(M, N, x, [(out, "out")], [(gamma, N, "gamma"), (x_scale, M, "x_scale")])
-    y = out if out is not None else _empty_like_out(x, M, N)
+    _validate(M, N, x, ((out, "out"),), ((gamma, N, "gamma"), (x_scale, M, "x_scale")))
+    y = out if out is not None else _empty_like_out(x)
     ys = _scale_out(x, M) if dt == FP8 else None
-    rstd = torch.empty(M, dtype=torch.float32, device=x.device) if save_stats else None
+    rstd = _scale_out(x, M) if save_stats else None
     s = h._stream()
-    pp = None if p is None else ctypes.byref(p)
-    _launch(h, "credit_rmsnorm_fwd", RMSNORM, FWD, dt, M, N, p, s,
-            lambda w, wn: (h.ptr, M, N, dt, _ptr(x), _ld(x), _ptr(x_scale), _ptr(gamma), float(eps), _ptr(y),
-                           _ld(y), _ptr(ys), _ptr(rstd), pp, w, wn, s))
+    w = h._call_ws(RMSNORM, FWD, dt, M, N, p, s)
+    check(lib().credit_rmsnorm_fwd(h.ptr, M, N, dt, x.data_ptr(), _ld(x), _ptr(x_scale), _ptr(gamma), float(eps),
+                                   y.data_ptr(), _ld(y), _ptr(ys), _ptr(rstd), _bref(p), w.data_ptr(), w.numel(), s),
+          "credit_rmsnorm_fwd")
     return y, ys, rstd
 
 
 def rmsnorm_bwd(x, dy, gamma, rstd=None, eps: float = 1e-5, x_scale=None, dy_scale=None,
                 p: Optional[Plan] = None, need_dgamma: bool = True, h: Optional[Handle] = None):
     """Returns (dx, dx_scale, dgamma); rstd None -> recomputed."""
-    torch = _torch()
     h = h or handle(x.device.index)
     dt = io_dtype(x)
     M, N = x.shape
-    _validate(M, N, x, [(dy, "dy")], [(gamma, N, "gamma"), (rstd, M, "rstd"), (x_scale, M, "x_scale"),
-                                     (dy_scale, M, "dy_scale")])
-    dx = _empty_like_out(x, M, N)
+    _validate(M, N, x, ((dy, "dy"),), ((gamma, N, "gamma"), (rstd, M, "rstd"), (x_scale, M, "x_scale"),
+                                       (dy_scale, M, "dy_scale")))
+    dx = _empty_like_out(x)
     dxs = _scale_out(x, M) if dt == FP8 else None
-    dg = torch.empty(N, dtype=torch.float32, device=x.device) if need_dgamma else None
+    dg = _scale_out(x, N) if need_dgamma else None
     s = h._stream()
-    pp = None if p is None else ctypes.byref(p)
-    _launch(h, "credit_rmsnorm_bwd", RMSNORM, BWD, dt, M, N, p, s,
-            lambda w, wn: (h.ptr, M, N, dt, _ptr(x), _ld(x), _ptr(x_scale), _ptr(dy), _ld(dy), _ptr(dy_scale),
-                           _ptr(gamma), _ptr(rstd), float(eps), _ptr(dx), _ld(dx), _ptr(dxs), _ptr(dg), pp, w, wn,
-                           s))
+    w = h._call_ws(RMSNORM, BWD, dt, M, N, p, s)
+    check(lib().credit_rmsnorm_bwd(h.ptr, M, N, dt, x.data_ptr(), _ld(x), _ptr(x_scale), dy.data_ptr(), _ld(dy),
+                                   _ptr(dy_scale), _ptr(gamma), _ptr(rstd), float(eps), dx.data_ptr(), _ld(dx),
+                                   _ptr(dxs), _ptr(dg), _bref(p), w.data_ptr(), w.numel(), s), "credit_rmsnorm_bwd")
     return dx, dxs, dg
 
 
@@ -652,14 +667,14 @@ def softmax_logits_bwd(x, dy, x_scale=None, dy_scale=None, p: Optional[Plan] = N
     h = h or handle(x.device.index)
     dt = io_dtype(x)
     M, N = x.shape
-    _validate(M, N, x, [(dy, "dy"), (out, "out")], [(x_scale, M, "x_scale"), (dy_scale, M, "dy_scale")])
-    dx = out if out is not None else _empty_like_out(x, M, N)
+    _validate(M, N, x, ((dy, "dy"), (out, "out")), ((x_scale, M, "x_scale"), (dy_scale, M, "dy_scale")))
+    dx = out if out is not None else _empty_like_out(x)
     dxs = _scale_out(x, M) if dt == FP8 else None
     s = h._stream()
-    pp = None if p is None else ctypes.byref(p)
-    _launch(h, "credit_softmax_logits_bwd", SOFTMAX_LOGITS, BWD, dt, M, N, p, s,
-            lambda w, wn: (h.ptr, M, N, dt, _ptr(x), _ld(x), _ptr(x_scale), _ptr(dy), _ld(dy), _ptr(dy_scale),
-                           _ptr(dx), _ld(dx), _ptr(dxs), pp, w, wn, s))
+    w = h._call_ws(SOFTMAX_LOGITS, BWD, dt, M, N, p, s)
+    check(lib().credit_softmax_logits_bwd(h.ptr, M, N, dt, x.data_ptr(), _ld(x), _ptr(x_scale), dy.data_ptr(),
+                                          _ld(dy), _ptr(dy_scale), dx.data_ptr(), _ld(dx), _ptr(dxs), _bref(p),
+                                          w.data_ptr(), w.numel(), s), "credit_softmax_logits_bwd")
     return dx, dxs
 
 
@@ -681,19 +696,18 @@ def quantize_rows(x, fmt: str = "int8", p: Optional[Plan] = None, out=None, out_
     """Row-wise quantisation of an FP32 / BF16 matrix.  fmt 'int8': codes
     torch.int8 in [-127, 127], scale = amax / 127; fmt 'fp8': e4m3 codes as
     torch.uint8, scale = amax / 448.  Returns (codes, scale)."""
-    torch = _torch()
     h = h or handle(x.device.index)
     dt = io_dtype(x)
     op = {"int8": QUANT_INT8, "fp8": QUANT_FP8}[fmt]
     M, N = x.shape
-    _validate(M, N, x, [], [(out_scale, M, "out_scale")])
+    _validate(M, N, x, (), ((out_scale, M, "out_scale"),))
     code_dt = _check_codes_out(out, M, N, fmt, x.device)
-    q = out if out is not None else torch.empty((M, N), dtype=code_dt, device=x.device)
+    q = out if out is not None else _torch_mod.empty((M, N), dtype=code_dt, device=x.device)
     qs = out_scale if out_scale is not None else _scale_out(x, M)
     s = h._stream()
-    pp = None if p is None else ctypes.byref(p)
-    _launch(h, "credit_quantize_rows", op, FWD, dt, M, N, p, s,
-            lambda w, wn: (h.ptr, op, M, N, dt, _ptr(x), _ld(x), _ptr(q), _ld(q), _ptr(qs), pp, w, wn, s))
+    w = h._call_ws(op, FWD, dt, M, N, p, s)
+    check(lib().credit_quantize_rows(h.ptr, op, M, N, dt, x.data_ptr(), _ld(x), q.data_ptr(), _ld(q), _ptr(qs),
+                                     _bref(p), w.data_ptr(), w.numel(), s), "credit_quantize_rows")
     return q, qs
 
 
@@ -701,20 +715,20 @@ def layernorm_fwd_fp8_out(x, gamma, beta, eps: float = 1e-5, p: Optional[Plan] =
                           h: Optional[Handle] = None):
     """LayerNorm forward of an FP32 / BF16 matrix fused with row-wise e4m3
     quantisation of y.  Returns (codes uint8, scale, mean, rstd)."""
-    torch = _torch()
     h = h or handle(x.device.index)
     dt = io_dtype(x)
     M, N = x.shape
-    _validate(M, N, x, [], [(gamma, N, "gamma"), (beta, N, "beta")])
+    _validate(M, N, x, (), ((gamma, N, "gamma"), (beta, N, "beta")))
+    torch = _torch_mod
     q = torch.empty((M, N), dtype=torch.uint8, device=x.device)
     qs = _scale_out(x, M)
-    mean = torch.empty(M, dtype=torch.float32, device=x.device) if save_stats else None
-    rstd = torch.empty(M, dtype=torch.float32, device=x.device) if save_stats else None
+    mean = _scale_out(x, M) if save_stats else None
+    rstd = _scale_out(x, M) if save_stats else None
     s = h._stream()
-    pp = None if p is None else ctypes.byref(p)
-    _launch(h, "credit_layernorm_fwd_fp8_out", LAYERNORM_FP8_OUT, FWD, dt, M, N, p, s,
-            lambda w, wn: (h.ptr, M, N, dt, _ptr(x), _ld(x), _ptr(gamma), _ptr(beta), float(eps), _ptr(q), _ld(q),
-                           _ptr(qs), _ptr(mean), _ptr(rstd), pp, w, wn, s))
+    w = h._call_ws(LAYERNORM_FP8_OUT, FWD, dt, M, N, p, s)
+    check(lib().credit_layernorm_fwd_fp8_out(h.ptr, M, N, dt, x.data_ptr(), _ld(x), _ptr(gamma), _ptr(beta), float(eps),
+                                             q.data_ptr(), _ld(q), _ptr(qs), _ptr(mean), _ptr(rstd), _bref(p),
+                                             w.data_ptr(), w.numel(), s), "credit_layernorm_fwd_fp8_out")
     return q, qs, mean, rstd
 
 
@@ -724,13 +738,13 @@ def pearson_bwd(x, y, dr, p: Optional[Plan] = None, h: Optional[Handle] = None):
     h = h or handle(x.device.index)
     dt = io_dtype(x)
     M, N = x.shape
-    _validate(M, N, x, [(y, "y")], [(dr, M, "dr")])
-    gx, gy = _empty_like_out(x, M, N), _empty_like_out(x, M, N)
+    _validate(M, N, x, ((y, "y"),), ((dr, M, "dr"),))
+    gx, gy = _empty_like_out(x), _empty_like_out(x)
     s = h._stream()
-    pp = None if p is None else ctypes.byref(p)
-    _launch(h, "credit_pearson_bwd", PEARSON, BWD, dt, M, N, p, s,
-            lambda w, wn: (h.ptr, M, N, dt, _ptr(x), _ld(x), _ptr(y), _ld(y), _ptr(dr), _ptr(gx), _ld(gx),
-                           _ptr(gy), _ld(gy), pp, w, wn, s))
+    w = h._call_ws(PEARSON, BWD, dt, M, N, p, s)
+    check(lib().credit_pearson_bwd(h.ptr, M, N, dt, x.data_ptr(), _ld(x), y.data_ptr(), _ld(y), _ptr(dr),
+                                   gx.data_ptr(), _ld(gx), gy.data_ptr(), _ld(gy), _bref(p), w.data_ptr(), w.numel(),
+                                   s), "credit_pearson_bwd")
     return gx, gy
 
 
@@ -740,13 +754,13 @@ def wvar_bwd(x, w, dv, p: Optional[Plan] = None, h: Optional[Handle] = None):
     h = h or handle(x.device.index)
     dt = io_dtype(x)
     M, N = x.shape
-    _validate(M, N, x, [(w, "w")], [(dv, M, "dv")])
-    gx, gw = _empty_like_out(x, M, N), _empty_like_out(x, M, N)
+    _validate(M, N, x, ((w, "w"),), ((dv, M, "dv"),))
+    gx, gw = _empty_like_out(x), _empty_like_out(x)
     s = h._stream()
-    pp = None if p is None else ctypes.byref(p)
-    _launch(h, "credit_wvar_bwd", WVAR, BWD, dt, M, N, p, s,
-            lambda ws, wn: (h.ptr, M, N, dt, _ptr(x), _ld(x), _ptr(w), _ld(w), _ptr(dv), _ptr(gx), _ld(gx),
-                            _ptr(gw), _ld(gw), pp, ws, wn, s))
+    ws = h._call_ws(WVAR, BWD, dt, M, N, p, s)
+    check(lib().credit_wvar_bwd(h.ptr, M, N, dt, x.data_ptr(), _ld(x), w.data_ptr(), _ld(w), _ptr(dv), gx.data_ptr(),
+                                _ld(gx), gw.data_ptr(), _ld(gw), _bref(p), ws.data_ptr(), ws.numel(), s),
+          "credit_wvar_bwd")
     return gx, gw
 
 
