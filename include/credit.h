@@ -49,7 +49,8 @@
  *     fills the cache with the configured selector's choice, timing kernels
  *     where that selector times), else the learned network's first legal
  *     choice, computed on the handle's stream in buffers allocated when the
- *     model was set (the fixed rule without a model).
+ *     model was set (the fixed rule without a model, and for the LayerNorm /
+ *     RMSNorm backward where the fixed rule's plan runs in the streaming form).
  *   - Operator calls may be recorded into a HIP graph (stream capture) and
  *     replayed: a recorded split-row launch is preceded by a one-thread kernel
  *     that advances a device-side exchange epoch, so every replay is a new
@@ -531,7 +532,11 @@ credit_status_t credit_set_epoch(uint32_t next_epoch);
 
 /* Launch geometry the library would use for a plan: grid size (workgroups),
  * threads per workgroup, per-thread vector count, co-resident workgroups per
- * CU, rows per workgroup.  Every output pointer is nullable.  Host-only. */
+ * CU, rows per workgroup.  Every output pointer is nullable.  Host-only.  A
+ * handle runs a resident / split plan in the streaming form (64 to 1024 threads
+ * per workgroup, parameters and column sums kept across the rows, the next
+ * rows loaded ahead) where that is faster, and reports that form; with
+ * h == NULL the geometry is that of the one-row kernels' register model. */
 credit_status_t credit_plan_geometry(credit_handle_t h, credit_op_t op, credit_dir_t dir,
                                      credit_dtype_t dt, int64_t M, int64_t N,
                                      const credit_plan_t *plan, int32_t *grid, int32_t *block,

@@ -22,6 +22,7 @@ namespace credit {
 const void *resident_kernel_softmax_fwd(int, int);
 const void *resident_kernel_ln_fwd(int, int);
 const void *multirow_kernel(int, int, int, int);
+const void *stream_kernel_bwd(int, int, int, int, bool, bool);
 const void *resident_kernel_rms_fwd(int, int);
 const void *resident_kernel_softmax_bwd(int, int);
 const void *resident_kernel_ln_bwd(int, int);
@@ -212,6 +213,7 @@ struct Launch {
     size_t shmem = 0;
     int64_t chunk = 0;
     bool xcd = false;
+    bool stream = false;  // the streaming kernel (stream.h); vpt and rows are its V and R
     int parts = 0, rowblocks = 0;  // dgamma/dbeta partial rows
     size_t off_slots = 0, off_colpart = 0, off_stats = 0, ws_bytes = 0;
 };
@@ -263,7 +265,7 @@ struct credit_handle_s {
     std::map<const void *, size_t> scratch;
     std::map<const void *, int> coresident;
     std::recursive_mutex lock;
-    std::map<const void *, int> occ_cache;
+    std::map<std::pair<const void *, int>, int> occ_cache;  // by (kernel, workgroup threads)
     std::map<std::tuple<int, int, int, int64_t, int64_t, int>, credit_plan_t> plan_cache;
     // timing arena
     char *arena = nullptr;
@@ -292,11 +294,11 @@ namespace {
 
 int occupancy(credit_handle_t h, const void *fn, int block, size_t shmem) {
     if (!h) return -1;
-    auto it = h->occ_cache.find(fn);
+    auto it = h->occ_cache.find({fn, block});
     if (it != h->occ_cache.end() && shmem == 0) return it->second;
     int n = 0;
     if (hipOccupancyMaxActiveBlocksPerMultiprocessor(&n, fn, block, shmem) != hipSuccess) return 0;
-    if (shmem == 0) h->occ_cache[fn] = n;
+    if (shmem == 0) h->occ_cache[{fn, block}] = n;
     return n;
 }
 
@@ -322,10 +324,11 @@ int rows_for(credit_handle_t h, int k_op, int dt, int vpt, int64_t M, int k, int
     return want;
 }
 
-// Resolves a plan into launch geometry and workspace layout.  Returns
-// CREDIT_ERR_UNSUPPORTED when the plan is illegal for the shape.
-credit_status_t resolve(credit_handle_t h, int k_op, int dt, int64_t M, int64_t N, credit_plan_t plan,
-                        bool recompute, Launch &L) {
+// Resolves a plan into the launch geometry and workspace layout of the
+// two-pass, one-row and multi-row kernels.  Returns CREDIT_ERR_UNSUPPORTED
+// when the plan is illegal for the shape.
+credit_status_t resolve_rows(credit_handle_t h, int k_op, int dt, int64_t M, int64_t N, credit_plan_t plan,
+                             Launch &L) {
     L = Launch();
     L.variant = plan.variant;
     const int epv = dt_epv(dt);
@@ -421,7 +424,108 @@ credit_status_t resolve(credit_handle_t h, int k_op, int dt, int64_t M, int64_t 
         off = align256(off + (size_t)L.groups * ncp * N * 4);
     }
     L.ws_bytes = off;
-    (void)recompute;
+    return CREDIT_OK;
+}
+
+const void *stream_fn(int k_op, int dt, int v, int r, bool split, bool full) {
+    return stream_kernel_bwd(k_op, dt, v, r, split, full);
+}
+
+// The streaming form (stream.h) of a slice of `cvec` vectors: V vectors per
+// lane, R rows per round and the most workgroups per CU (0: as many as fit).
+// v == 0: the one-row kernel is kept.
+struct StreamForm {
+    int v = 0, r = 0, cap = 0;
+};
+
+// LayerNorm / RMSNorm backward, back to back on MI355X (us, one-row kernel ->
+// streaming form, column sums included).  Row-resident: one to four waves per
+// SIMD-quarter are enough with the next round in flight, and more workgroups
+// only write more partial rows of dgamma / dbeta, so the workgroups per CU are
+// capped at 8 (V = 1) or 4 (V = 2) waves: BF16 16384 x 1024 44.6 -> 27.8 (33.0
+// at 6 workgroups per CU), 8192 x 2048 33.8 -> 27.7, 8192 x 4096 52.1 -> 41.5
+// (48.6 uncapped), 8192 x 8192 97.2 -> 78.2, ragged 3001 x 7777 95.9 -> 45.6, FP32
+// 4095 x 5003 77.8 -> 52.1.  Split: as many workgroups as fit, to cover the
+// exchange: BF16 2048 x 131072 k = 16 384 -> 342 (LayerNorm), 359 -> 306 (RMSNorm),
+// 4096 x 16384 k = 4 107 -> 88, k = 8 135 -> 91, k = 32 580 -> 154.  FP32 LayerNorm
+// slices over 1024 vectors keep the one-row kernel (2048 x 131072 k = 16: 602
+// against 622; RMSNorm 610 -> 561), and so do BF16 RMSNorm ones (k = 8: 345 against
+// 380).
+StreamForm stream_form_norm_bwd(int k_op, int dt, int k, int64_t cvec) {
+    const bool ln = k_op == OP_LN_BWD, f32 = dt == CREDIT_F32;
+    const int w1 = (int)((cvec + 63) / 64), w2 = (int)((cvec + 127) / 128);
+    if (k == 1) {
+        if (cvec <= 256) return {1, 4, std::max(2, 8 / w1)};
+        if (cvec <= 1024) return {2, 2, std::max(1, 4 / w2)};
+        if (cvec <= 2048) return {4, 1, 1};
+        return {};
+    }
+    if (cvec <= 128 || (cvec <= 256 && ln && !f32)) return {1, 4, 0};
+    if (cvec <= 256) return {1, 2, 0};
+    if (cvec <= 512 || (cvec <= 1024 && (f32 || !ln))) return {2, 2, 0};
+    if (cvec <= 1024) return {2, 4, 0};
+    if (cvec <= 2048 && f32 && !ln) return {4, 1, 0};
+    return {};
+}
+
+// Replaces a resident / split plan's kernel by the streaming one where that is
+// faster: FP32 / BF16 rows of at least one vector, and enough rows that every
+// row group has a full round (with fewer there is nothing to stream, and the
+// one-row kernel spreads them over more workgroups).
+void resolve_stream(credit_handle_t h, int k_op, int dt, int64_t M, int64_t N, Launch &L) {
+    const int epv = dt_epv(dt);
+    if (dt == CREDIT_FP8_E4M3 || N < epv) return;
+    const int64_t cvec = L.chunk / epv;
+    StreamForm f;
+    if (k_op == OP_LN_BWD || k_op == OP_RMS_BWD) f = stream_form_norm_bwd(k_op, dt, L.k, cvec);
+    if (!f.v) return;
+    const int w = (int)((cvec + 64 * f.v - 1) / (64 * f.v));
+    const void *fn = stream_fn(k_op, dt, f.v, f.r, L.k > 1, N == (int64_t)L.k * f.v * w * 64 * epv);
+    if (!fn) return;
+    int occ = occupancy(h, fn, w * 64, 0);
+    if (f.cap) occ = std::min(occ, f.cap);
+    int64_t gmax = (int64_t)occ * h->cus / L.k;
+    if (h->max_groups > 0) gmax = std::min<int64_t>(gmax, h->max_groups);
+    if (L.k > 1 && gmax >= 8) gmax = gmax / 8 * 8;  // XCD-aware member mapping (see resolve_rows)
+    const int64_t blocks = (M + f.r - 1) / f.r;
+    if (gmax < 1 || blocks < gmax) return;
+    // as few groups as finish in the same number of rounds
+    const int64_t rounds = (blocks + gmax - 1) / gmax;
+    int64_t groups = (blocks + rounds - 1) / rounds;
+    if (L.k > 1 && gmax >= 8) groups = (groups + 7) / 8 * 8;
+    L.stream = true;
+    L.fn = fn;
+    L.vpt = f.v;
+    L.rows = f.r;
+    L.block = w * 64;
+    L.per_cu = occ;
+    L.groups = (int)groups;
+    L.grid = (int)(groups * L.k);
+    L.xcd = L.k > 1 && gmax >= 8;
+    const int ncp = ncp_of(k_op);
+    size_t off = 256;
+    if (L.k > 1) {  // slots by row, as in the one-row kernel
+        L.off_slots = off;
+        off = align256(off + (size_t)M * kMaxStages * L.k * q_of(k_op) * 8);
+    }
+    if (ncp) {
+        L.parts = L.groups;
+        L.off_colpart = off;
+        off = align256(off + (size_t)L.groups * ncp * N * 4);
+    }
+    L.ws_bytes = off;
+}
+
+// The launch of a plan; see resolve_rows and resolve_stream.
+credit_status_t resolve(credit_handle_t h, int k_op, int dt, int64_t M, int64_t N, credit_plan_t plan, bool recompute,
+                        Launch &L) {
+    const credit_status_t st = resolve_rows(h, k_op, dt, M, N, plan, L);
+    if (st != CREDIT_OK || !h || plan.variant == CREDIT_TWO_PASS || M < 1) return st;
+    Launch S = L;
+    resolve_stream(h, k_op, dt, M, N, S);
+    // the workspace holds either form's: a caller sizes it once for both
+    S.ws_bytes = L.ws_bytes = std::max(L.ws_bytes, S.ws_bytes);
+    if (S.stream && !recompute) L = S;
     return CREDIT_OK;
 }
 
@@ -506,7 +610,7 @@ credit_status_t issue(credit_handle_t h, const OpCall &c, const Launch &L, void 
     a.in0 = c.in0; a.in1 = c.in1; a.out = c.out; a.out1 = c.out1;
     a.ld0 = c.ld0; a.ld1 = c.ld1; a.ldo = c.ldo; a.ldo1 = c.ldo1;
     a.rowg = c.rowg;
-    a.qs = q_of(c.k_op) * L.rows;
+    a.qs = q_of(c.k_op) * (L.stream ? 1 : L.rows);  // the streaming kernel's slots are per row
     a.s0 = c.s0; a.s1 = c.s1; a.so = c.so;
     a.gamma = c.gamma; a.beta = c.beta;
     a.mean_in = c.mean_in; a.rstd_in = c.rstd_in;
@@ -1097,6 +1201,17 @@ credit_status_t analytic_pick(credit_handle_t h, int k_op, int dt, int64_t M, in
 // exchange traffic that grows with k), the two-pass plan rereads them.
 int bytes_rank(int c) { return c == 0 ? CREDIT_NUM_PLANS : c; }
 
+// Whether the fixed rule's plan of the shape runs in the streaming form, which
+// the network's training timings predate.  The normalisation backward is then
+// fastest with the fewest members a row needs (BF16 LayerNorm 4096 x 5120: 34 us
+// resident, 46 at the network's k = 2; 4096 x 16384: 88 at k = 2 and 4, 91 at 8), so
+// a call without a plan takes the fixed rule's.
+bool stream_default(credit_handle_t h, int k_op, int dt, int64_t M, int64_t N) {
+    if (k_op != OP_LN_BWD && k_op != OP_RMS_BWD) return false;
+    Launch L;
+    return resolve(h, k_op, dt, M, N, fixed_rule(h, k_op, dt, M, N), false, L) == CREDIT_OK && L.stream;
+}
+
 // Every legal plan timed (cache flush, median of 15).  The fastest median is
 // the best plan, except that plans within the timing noise of it --
 // max(1%, 2 MAD of either) -- count as equally fast, and among those the one
@@ -1211,7 +1326,7 @@ credit_status_t pick_plan(credit_handle_t h, int k_op, int dt, int64_t M, int64_
             return CREDIT_OK;
         }
         st = CREDIT_ERR_MODEL;
-        if (sel != CREDIT_SEL_FIXED && h->has_model && core_op(k_op))
+        if (sel != CREDIT_SEL_FIXED && h->has_model && core_op(k_op) && !stream_default(h, k_op, dt, M, N))
             st = learned_pick(h, k_op, dt, M, N, false, out, pred);
         if (st != CREDIT_OK) *out = fixed_rule(h, k_op, dt, M, N);
         h->plan_cache[key] = *out;
