@@ -432,7 +432,9 @@ __device__ __forceinline__ void row_loop(const RowArgs &a, int c, int grp, const
                 decode<DT>(t0, q, 1.f);
                 for (int i = 0; i < tn; ++i) qmax = fmaxf(qmax, q[i]);
             }
-            float st[2] = {qmax == -INFINITY ? -INFINITY : qmax * K, 0.f};
+            // held finite for a thread whose elements are all the type's lowest
+            // value (a mask): its exponentials would be inf, and inf * 0 NaN
+            float st[2] = {qmax == -INFINITY ? -INFINITY : fmaxf(qmax * K, -0x1.fffffep+127f), 0.f};
             const float ct = qmax == -INFINITY ? 0.f : st[0];
             fresh();
 #pragma unroll
@@ -1036,7 +1038,7 @@ __device__ __forceinline__ void row_loop(const RowArgs &a, int c, int grp, const
                 decode<DT>(t0, q, 1.f);
                 for (int i = 0; i < tn; ++i) qmax = fmaxf(qmax, q[i]);
             }
-            float st[3] = {qmax == -INFINITY ? -INFINITY : qmax * K, 0.f, 0.f};
+            float st[3] = {qmax == -INFINITY ? -INFINITY : fmaxf(qmax * K, -0x1.fffffep+127f), 0.f, 0.f};  // as in the forward
             const float ct = qmax == -INFINITY ? 0.f : st[0];
             fresh();
 #pragma unroll
