@@ -23,6 +23,8 @@ const void *resident_kernel_softmax_fwd(int, int);
 const void *resident_kernel_ln_fwd(int, int);
 const void *multirow_kernel(int, int, int, int);
 const void *stream_kernel_bwd(int, int, int, int, bool, bool);
+const void *stream_kernel_ln_fwd(int, int, int, bool, bool);
+const void *stream_kernel_rms_fwd(int, int, int, bool, bool);
 const void *resident_kernel_rms_fwd(int, int);
 const void *resident_kernel_softmax_bwd(int, int);
 const void *resident_kernel_ln_bwd(int, int);
@@ -428,7 +430,13 @@ credit_status_t resolve_rows(credit_handle_t h, int k_op, int dt, int64_t M, int
 }
 
 const void *stream_fn(int k_op, int dt, int v, int r, bool split, bool full) {
-    return stream_kernel_bwd(k_op, dt, v, r, split, full);
+    switch (k_op) {
+    case OP_LN_BWD:
+    case OP_RMS_BWD: return stream_kernel_bwd(k_op, dt, v, r, split, full);
+    case OP_LN_FWD: return stream_kernel_ln_fwd(dt, v, r, split, full);
+    case OP_RMS_FWD: return stream_kernel_rms_fwd(dt, v, r, split, full);
+    default: return nullptr;
+    }
 }
 
 // The streaming form (stream.h) of a slice of `cvec` vectors: V vectors per
@@ -436,6 +444,7 @@ const void *stream_fn(int k_op, int dt, int v, int r, bool split, bool full) {
 // v == 0: the one-row kernel is kept.
 struct StreamForm {
     int v = 0, r = 0, cap = 0;
+    bool many = false;  // row-resident: only for more than two rounds
 };
 
 // LayerNorm / RMSNorm backward, back to back on MI355X (us, one-row kernel ->
@@ -468,19 +477,66 @@ StreamForm stream_form_norm_bwd(int k_op, int dt, int k, int64_t cvec) {
     return {};
 }
 
+// LayerNorm / RMSNorm forward, as above (us).  `whole`: every slice is whole
+// vectors of every lane.  Row-resident: short rows need no barrier and read
+// gamma / beta once per workgroup, not once or twice per row: BF16 LayerNorm
+// 16384 x 1024 42 -> 13.7, 8192 x 4096 31.2 -> 26.6, 8192 x 5120 45 -> 34, RMSNorm 35 ->
+// 31.5, ragged 8192 x 3001 36 -> 22, FP32 4095 x 5003 44 -> 33 and 37.5 -> 33; 4096 x
+// 16384 BF16 53 -> 49 and 50 -> 46, FP32 98 -> 94.  Two rounds of long rows are too
+// few to pay for the longer start unless the one-row kernel's rows are ragged
+// (FP32 1024 x 8192 9.9 against 12.0; 256 x 16385 BF16 12.2 -> 9.2).  Split: BF16 2048
+// x 131072 k = 8 238 -> 198 (LayerNorm), 198 -> 181, k = 16 244 -> 221 and 195 -> 196;
+// ragged 2048 x 100001 k = 8 282 -> 200 and 242 -> 170; 4096 x 16384 k = 8 166 -> 57.
+// FP32 slices over 1024 vectors win only with few members (1024 x 131072 k = 8 190
+// -> 188, k = 16 185 against 188; ragged 1024 x 131073 k = 16 257 against 287) and BF16
+// ones over 2048 only where rows are ragged (2048 x 131072 k = 4 217 against 225).
+StreamForm stream_form_norm_fwd(int k_op, int dt, int k, int64_t cvec, bool whole, bool aligned) {
+    const bool ln = k_op == OP_LN_FWD, f32 = dt == CREDIT_F32;
+    if (k == 1) {
+        if (cvec <= 256 && !f32) return {2, 4, 0};
+        if (cvec <= 1024) return {2, 2, 0};
+        if (cvec <= 2048) return {4, 1, 0, aligned};
+        if (cvec <= 4096) return {8, 1, 0, aligned};
+        return {};
+    }
+    if (cvec <= 128 || (cvec <= 256 && (f32 || !ln))) return {1, 4, 0};
+    if (cvec <= 256) return {2, 4, 0};
+    if (f32) {
+        if (cvec <= 512) return !whole ? StreamForm{2, 4, 0} : ln ? StreamForm{1, 4, 0} : StreamForm{2, 2, 0};
+        if (cvec <= 1024) return ln ? StreamForm{2, 2, 0} : StreamForm{2, 4, 0};
+        if (cvec <= 2048 && k <= 4) return {4, 1, 0};
+        if (cvec <= 4096 && k >= 4 && k <= 8) return {8, 1, 0};
+        return {};
+    }
+    if (cvec <= 512) return {2, 2, 0};
+    if (cvec <= 1024) return whole && !ln ? StreamForm{2, 4, 0} : StreamForm{2, 2, 0};
+    if (cvec <= 2048) return whole ? StreamForm{4, 1, 0} : StreamForm{2, 2, 0};
+    if (cvec <= 4096 && !whole) return {8, 1, 0};
+    return {};
+}
+
 // Replaces a resident / split plan's kernel by the streaming one where that is
-// faster: FP32 / BF16 rows of at least one vector, and enough rows that every
-// row group has a full round (with fewer there is nothing to stream, and the
-// one-row kernel spreads them over more workgroups).
+// faster: FP32 / BF16 rows of at least one vector, and enough rows -- a workgroup
+// for every CU of a row-resident plan (its waves work alone or in small groups,
+// so it leads before there is a second round to stream: BF16 softmax 4096 x 1000
+// 12 -> 6.5 us, LayerNorm 1024 x 5120 9.2 -> 7.0, RMSNorm backward 1024 x 2048 12.1 ->
+// 8.3; 512 rows of 2048 are even), and of a split one a full round for every row
+// group (backward) or more than two (BF16 softmax backward from the logits 300 x
+// 32768 k = 8, two rounds: 18.5 against 23).
 void resolve_stream(credit_handle_t h, int k_op, int dt, int64_t M, int64_t N, Launch &L) {
     const int epv = dt_epv(dt);
     if (dt == CREDIT_FP8_E4M3 || N < epv) return;
+    if (h->rows_opt && (k_op == OP_LN_FWD || k_op == OP_RMS_FWD)) return;
     const int64_t cvec = L.chunk / epv;
     StreamForm f;
     if (k_op == OP_LN_BWD || k_op == OP_RMS_BWD) f = stream_form_norm_bwd(k_op, dt, L.k, cvec);
+    if (k_op == OP_LN_FWD || k_op == OP_RMS_FWD)
+        f = stream_form_norm_fwd(k_op, dt, L.k, cvec, N == L.k * cvec * epv && cvec % 512 == 0, N % epv == 0);
     if (!f.v) return;
-    const int w = (int)((cvec + 64 * f.v - 1) / (64 * f.v));
-    const void *fn = stream_fn(k_op, dt, f.v, f.r, L.k > 1, N == (int64_t)L.k * f.v * w * 64 * epv);
+    int w = (int)((cvec + 64 * f.v - 1) / (64 * f.v));
+    const bool full = N == (int64_t)L.k * f.v * w * 64 * epv;
+    if (w > stream_max_waves(k_op, dt, f.v, f.r)) return;
+    const void *fn = stream_fn(k_op, dt, f.v, f.r, L.k > 1, full);
     if (!fn) return;
     int occ = occupancy(h, fn, w * 64, 0);
     if (f.cap) occ = std::min(occ, f.cap);
@@ -488,11 +544,33 @@ void resolve_stream(credit_handle_t h, int k_op, int dt, int64_t M, int64_t N, L
     if (h->max_groups > 0) gmax = std::min<int64_t>(gmax, h->max_groups);
     if (L.k > 1 && gmax >= 8) gmax = gmax / 8 * 8;  // XCD-aware member mapping (see resolve_rows)
     const int64_t blocks = (M + f.r - 1) / f.r;
-    if (gmax < 1 || blocks < gmax) return;
-    // as few groups as finish in the same number of rounds
-    const int64_t rounds = (blocks + gmax - 1) / gmax;
-    int64_t groups = (blocks + rounds - 1) / rounds;
-    if (L.k > 1 && gmax >= 8) groups = (groups + 7) / 8 * 8;
+    if (gmax < 1) return;
+    const bool bwd = k_op == OP_LN_BWD || k_op == OP_RMS_BWD;
+    if (L.k > 1 ? blocks < gmax || (!bwd && blocks <= 2 * gmax)
+                : blocks < std::min<int64_t>(gmax, h->cus) || (f.many && blocks <= 2 * gmax))
+        return;
+    int64_t groups = 0;
+    if (L.k > 1) {
+        // as few groups as finish in the same number of rounds
+        const int64_t rounds = (blocks + gmax - 1) / gmax;
+        groups = (blocks + rounds - 1) / rounds;
+        if (gmax >= 8) groups = (groups + 7) / 8 * 8;
+    } else {
+        // Of all groups that finish in the same number of rounds the fewest;
+        // and of those numbers of workgroups per CU, down to half of what fits,
+        // the one that leaves the busiest CU the fewest rounds (1366 groups of 3
+        // rounds are 5.3 per CU, so some CUs work 18 rounds; 1024 of 4 work 16).
+        int64_t least = INT64_MAX;
+        for (int p = occ; p >= (occ + 1) / 2; --p) {
+            const int64_t g = std::min<int64_t>(gmax, (int64_t)p * h->cus);
+            const int64_t rounds = (blocks + g - 1) / g, n = (blocks + rounds - 1) / rounds;
+            const int64_t busiest = (n + h->cus - 1) / h->cus * rounds;
+            if (busiest < least) {
+                least = busiest;
+                groups = n;
+            }
+        }
+    }
     L.stream = true;
     L.fn = fn;
     L.vpt = f.v;
@@ -1202,12 +1280,13 @@ credit_status_t analytic_pick(credit_handle_t h, int k_op, int dt, int64_t M, in
 int bytes_rank(int c) { return c == 0 ? CREDIT_NUM_PLANS : c; }
 
 // Whether the fixed rule's plan of the shape runs in the streaming form, which
-// the network's training timings predate.  The normalisation backward is then
-// fastest with the fewest members a row needs (BF16 LayerNorm 4096 x 5120: 34 us
-// resident, 46 at the network's k = 2; 4096 x 16384: 88 at k = 2 and 4, 91 at 8), so
-// a call without a plan takes the fixed rule's.
+// the network's training timings predate.  Rows are then fastest with the
+// fewest members they need (BF16 LayerNorm backward 4096 x 5120: 34 us resident,
+// 46 at the network's k = 2; 4096 x 16384: 88 at k = 2 and 4, 91 at 8; forward 4096 x
+// 16384 FP32 93.8 resident, 95.8 at k = 2), so a call without a plan takes the
+// fixed rule's.
 bool stream_default(credit_handle_t h, int k_op, int dt, int64_t M, int64_t N) {
-    if (k_op != OP_LN_BWD && k_op != OP_RMS_BWD) return false;
+    if (!core_op(k_op)) return false;
     Launch L;
     return resolve(h, k_op, dt, M, N, fixed_rule(h, k_op, dt, M, N), false, L) == CREDIT_OK && L.stream;
 }

@@ -103,6 +103,25 @@ constexpr int wave_override(int op, int dt, int vpt) {
          : (dt == DT_F32 && vpt == 4) ? 4 : 0;
 }
 
+// The streaming kernels (stream.h): most waves of a workgroup.
+constexpr int kStreamWaves = 16;
+
+// Parameter vectors held in registers.
+constexpr int stream_params(int op) { return op == OP_LN_FWD ? 2 : (op == OP_RMS_FWD || op == OP_LN_BWD || op == OP_RMS_BWD) ? 1 : 0; }
+constexpr int stream_ncp(int op) { return op == OP_LN_BWD ? 2 : op == OP_RMS_BWD ? 1 : 0; }
+// Registers a lane needs: two buffers of R rows, parameters, column sums.
+constexpr int stream_regs(int op, int dt, int v, int r) {
+    const int epv = dt == DT_F32 ? 4 : 8;
+    return 2 * r * v * 4 * (two_in(op) ? 2 : 1) + v * epv * (stream_params(op) + stream_ncp(op)) + 48;
+}
+// Most waves of a workgroup: its registers have to fit the CU's 4 x 512.
+constexpr int stream_max_waves(int op, int dt, int v, int r) { return stream_regs(op, dt, v, r) <= 112 ? 16 : 8; }
+
+// Softmax and its backward from the logits (stream_softmax.h).
+constexpr bool softmax_stream(int op) { return op == OP_SOFTMAX_FWD || op == OP_SMXL_BWD; }
+// Their forms of long rows begin each row's vectors on the row's first line.
+constexpr bool stream_phase(int op, int v) { return softmax_stream(op) && v >= 4; }
+
 struct RowArgs {
     const void *in0;   // x (forward, norm backward) or y (softmax backward)
     const void *in1;   // dy (backward); y (Pearson); w (weighted variance)

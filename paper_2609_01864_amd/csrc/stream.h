@@ -26,32 +26,16 @@
 // at a time, in wave 0 (the slots are those of the one-row kernels), and
 // merges the members in its lanes in the same way.
 //
-// Bound: HBM where the rows are long enough (BF16 RMSNorm backward 8192 x 8192:
-// 5.4 TB/s of 6.45); the exchange, whose polls return in order behind the next
-// round's loads, on split rows (2048 x 131072 k = 16: 4.7-5.3 TB/s); the column
-// sums' partial rows on narrow ones.  Before and after at each rule in host.cpp.
+// Bound: HBM where the rows are long enough (BF16 RMSNorm forward 8192 x 4096 and
+// backward 8192 x 8192: 5.4 TB/s of 6.45); the exchange, whose polls return in
+// order behind the next round's loads, on split rows (backward 2048 x 131072 k = 16:
+// 4.7-5.3 TB/s); the column sums' partial rows on narrow ones of the backward;
+// arithmetic and the launch on the forward's shortest (16384 x 1024 13.7 us for a
+// floor of 10.4).  Before and after at each rule in host.cpp.
 #pragma once
 #include "resident.h"
 
 namespace credit {
-
-constexpr int kStreamWaves = 16;  // most waves of a workgroup
-
-// Operators that have a streaming form (FP32 / BF16 rows).
-constexpr bool stream_op(int op) {
-    return op == OP_LN_BWD || op == OP_RMS_BWD || op == OP_LN_FWD || op == OP_RMS_FWD || op == OP_SOFTMAX_FWD ||
-           op == OP_SMXL_BWD || op == OP_SOFTMAX_BWD;
-}
-// Parameter vectors held in registers.
-constexpr int stream_params(int op) { return op == OP_LN_FWD ? 2 : (op == OP_RMS_FWD || op == OP_LN_BWD || op == OP_RMS_BWD) ? 1 : 0; }
-constexpr int stream_ncp(int op) { return op == OP_LN_BWD ? 2 : op == OP_RMS_BWD ? 1 : 0; }
-// Registers a lane needs: two buffers of R rows, parameters, column sums.
-constexpr int stream_regs(int op, int dt, int v, int r) {
-    const int epv = dt == DT_F32 ? 4 : 8;
-    return 2 * r * v * 4 * (two_in(op) ? 2 : 1) + v * epv * (stream_params(op) + stream_ncp(op)) + 48;
-}
-// Most waves of a workgroup: its registers have to fit the CU's 4 x 512.
-constexpr int stream_max_waves(int op, int dt, int v, int r) { return stream_regs(op, dt, v, r) <= 112 ? 16 : 8; }
 
 // Workgroup barrier that orders LDS only: global loads and stores in flight
 // stay in flight across it.
@@ -627,109 +611,6 @@ __device__ __forceinline__ void stream_rows(const RowArgs &a, int c, int grp, St
                     }
                     store(row0 + i, i < nr, j, encode<DT>(dx, 1.f));
                     __builtin_amdgcn_sched_barrier(0);
-                }
-            }
-        } else if constexpr (OP == OP_SOFTMAX_BWD) {
-            float st[R][1];
-#pragma unroll
-            for (int i = 0; i < R; ++i) {
-                float s = 0.f;
-#pragma unroll
-                for (int j = 0; j < V; ++j) {
-                    if (!FULL && j > jp) continue;
-                    mask(x0[i][j], j, 0u);
-                    mask(x1[i][j], j, 0u);
-                    float y[EPV], g[EPV];
-                    decode<DT>(x0[i][j], y, 1.f);
-                    decode<DT>(x1[i][j], g, 1.f);
-#pragma unroll
-                    for (int e = 0; e < EPV; ++e) s = fmaf(g[e], y[e], s);
-                    keep_order(s);
-                }
-                st[i][0] = wave_sum(s);
-            }
-            stream_reduce<OP, R, SPLIT>(st, a, row0, nr, c, lds, parity);
-            fresh();
-#pragma unroll
-            for (int i = 0; i < R; ++i) {
-#pragma unroll
-                for (int j = 0; j < V; ++j) {
-                    float y[EPV], g[EPV], dx[EPV];
-                    decode<DT>(x0[i][j], y, 1.f);
-                    decode<DT>(x1[i][j], g, 1.f);
-#pragma unroll
-                    for (int e = 0; e < EPV; ++e) dx[e] = y[e] * (g[e] - st[i][0]);
-                    store(row0 + i, i < nr, j, encode<DT>(dx, 1.f));
-                }
-            }
-        } else {
-            // softmax forward, and its backward from the logits: exponentials
-            // about the wave's maximum; the sums of the waves (and members)
-            // are rescaled when merged.  Elements that are not the lane's own
-            // are -inf (and their dy 0), so they add nothing.
-            constexpr bool BW = OP == OP_SMXL_BWD;
-            constexpr unsigned NINF = DT == DT_F32 ? 0xff800000u : 0xff80ff80u;
-            float st[R][S::NS], ct[R];
-#pragma unroll
-            for (int i = 0; i < R; ++i) {
-                float qmax = -INFINITY;
-#pragma unroll
-                for (int j = 0; j < V; ++j) {
-                    if (!FULL && j > jp) continue;
-                    mask(x0[i][j], j, NINF);
-                    if constexpr (BW) mask(x1[i][j], j, 0u);
-                    float q[EPV];
-                    decode<DT>(x0[i][j], q, 1.f);
-#pragma unroll
-                    for (int e = 0; e < EPV; ++e) qmax = fmaxf(qmax, q[e]);
-                    keep_order(qmax);
-                }
-                opaque<V>(x0[i]);
-                qmax = wave_max(qmax);
-                st[i][0] = qmax == -INFINITY ? -INFINITY : qmax * kLog2e;
-                ct[i] = qmax == -INFINITY ? 0.f : st[i][0];
-                float s = 0.f, t = 0.f;
-#pragma unroll
-                for (int j = 0; j < V; ++j) {
-                    if (!FULL && j > jp) continue;
-                    float q[EPV], g[EPV];
-                    decode<DT>(x0[i][j], q, 1.f);
-                    if constexpr (BW) decode<DT>(x1[i][j], g, 1.f);
-#pragma unroll
-                    for (int e = 0; e < EPV; ++e) {
-                        const float ev = fast_exp2(fmaf(q[e], kLog2e, -ct[i]));
-                        s += ev;
-                        if constexpr (BW) t = fmaf(ev, g[e], t);
-                        else if constexpr (DT == DT_F32) x0[i][j][e] = __float_as_uint(ev);
-                    }
-                    keep_order(s, t);
-                }
-                st[i][1] = wave_sum(s);
-                if constexpr (BW) st[i][S::NS - 1] = wave_sum(t);
-            }
-            stream_reduce<OP, R, SPLIT>(st, a, row0, nr, c, lds, parity);
-            fresh();
-#pragma unroll
-            for (int i = 0; i < R; ++i) {
-                const float cmax = st[i][0], inv_s = 1.f / st[i][1];
-                const float csh = kExpShift - cmax, mul = inv_s * kExpUnshift;
-                const float cdot = BW ? st[i][S::NS - 1] * inv_s : 0.f;
-                // FP32 forward: the kept exponentials times one factor; the
-                // clamp keeps it finite for a wave without a finite element
-                // (see resident.h)
-                const float f = fast_exp2(fminf(ct[i] + csh, 64.f)) * mul;
-#pragma unroll
-                for (int j = 0; j < V; ++j) {
-                    float q[EPV], y[EPV], g[EPV];
-                    decode<DT>(x0[i][j], q, 1.f);
-                    if constexpr (BW) decode<DT>(x1[i][j], g, 1.f);
-#pragma unroll
-                    for (int e = 0; e < EPV; ++e) {
-                        if constexpr (BW) y[e] = fast_exp2(fmaf(q[e], kLog2e, csh)) * mul * (g[e] - cdot);
-                        else if constexpr (DT == DT_F32) y[e] = q[e] * f;
-                        else y[e] = fast_exp2(fmaf(q[e], kLog2e, csh)) * mul;
-                    }
-                    store(row0 + i, i < nr, j, encode<DT>(y, 1.f));
                 }
             }
         }
