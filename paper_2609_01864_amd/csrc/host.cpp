@@ -25,6 +25,8 @@ const void *multirow_kernel(int, int, int, int);
 const void *stream_kernel_bwd(int, int, int, int, bool, bool);
 const void *stream_kernel_ln_fwd(int, int, int, bool, bool);
 const void *stream_kernel_rms_fwd(int, int, int, bool, bool);
+const void *stream_kernel_softmax(int, int, int, bool, bool);
+const void *stream_kernel_smxl_bwd(int, int, int, bool, bool);
 const void *resident_kernel_rms_fwd(int, int);
 const void *resident_kernel_softmax_bwd(int, int);
 const void *resident_kernel_ln_bwd(int, int);
@@ -435,6 +437,8 @@ const void *stream_fn(int k_op, int dt, int v, int r, bool split, bool full) {
     case OP_RMS_BWD: return stream_kernel_bwd(k_op, dt, v, r, split, full);
     case OP_LN_FWD: return stream_kernel_ln_fwd(dt, v, r, split, full);
     case OP_RMS_FWD: return stream_kernel_rms_fwd(dt, v, r, split, full);
+    case OP_SOFTMAX_FWD: return stream_kernel_softmax(dt, v, r, split, full);
+    case OP_SMXL_BWD: return stream_kernel_smxl_bwd(dt, v, r, split, full);
     default: return nullptr;
     }
 }
@@ -515,6 +519,26 @@ StreamForm stream_form_norm_fwd(int k_op, int dt, int k, int64_t cvec, bool whol
     return {};
 }
 
+// Softmax forward and backward from the logits, as above (us).  `lines`: rows
+// are whole 128-byte lines.  Row-resident: 16384 x 1000 BF16 37.5 -> 15 and 46 ->
+// 22, FP32 33.5 -> 26; 8192 x 3000 BF16 29.6 -> 22.8; 4096 x 16385 70 -> 62 and 122 ->
+// 86; 2048 x 50257 forward 107 -> 82 (98 with the vectors counted from the row's
+// start).  Split: 2048 x 50257 k = 2 111 -> 93 and 184 -> 130, k = 4 106 -> 91 and 173
+// -> 132, FP32 forward k = 4 154 -> 145; 8192 x 3000 k = 2 55 -> 36 and 66 -> 43. Slices
+// over 512 vectors keep the one-row kernels where rows are whole lines (2048 x
+// 32768 k = 2 51.7 against 53.6 and 76 against 80), as do FP32 ones of the backward
+// (2048 x 50257 k = 8 224 against 232).
+StreamForm stream_form_softmax(int k_op, int dt, int k, int64_t cvec, bool lines) {
+    const bool fwd = k_op == OP_SOFTMAX_FWD;
+    if (cvec <= (fwd || k == 1 ? 64 : 640)) return {1, 2, 0};
+    if (cvec <= 512) return {2, 2, 0};
+    if (k > 1 && (lines || (dt == CREDIT_F32 && !fwd))) return {};
+    // up to 8 vectors more than the slice's (stream_softmax.h)
+    if (cvec + 9 <= 4096) return {4, 1, 0};
+    if (fwd && cvec + 9 <= 8192) return {8, 1, 0};
+    return {};
+}
+
 // Replaces a resident / split plan's kernel by the streaming one where that is
 // faster: FP32 / BF16 rows of at least one vector, and enough rows -- a workgroup
 // for every CU of a row-resident plan (its waves work alone or in small groups,
@@ -532,9 +556,18 @@ void resolve_stream(credit_handle_t h, int k_op, int dt, int64_t M, int64_t N, L
     if (k_op == OP_LN_BWD || k_op == OP_RMS_BWD) f = stream_form_norm_bwd(k_op, dt, L.k, cvec);
     if (k_op == OP_LN_FWD || k_op == OP_RMS_FWD)
         f = stream_form_norm_fwd(k_op, dt, L.k, cvec, N == L.k * cvec * epv && cvec % 512 == 0, N % epv == 0);
+    if (softmax_stream(k_op)) f = stream_form_softmax(k_op, dt, L.k, cvec, N % (16 * epv) == 0);
     if (!f.v) return;
+    // vectors of a slice: the softmax family's rows begin up to 126 bytes into
+    // their first line (stream_softmax.h), and its slices are whole lines
     int w = (int)((cvec + 64 * f.v - 1) / (64 * f.v));
     const bool full = N == (int64_t)L.k * f.v * w * 64 * epv;
+    int64_t cv = cvec;
+    if (!full && stream_phase(k_op, f.v)) {
+        cv = ((N * dt_bytes(dt) + 126 + 15) / 16 + L.k - 1) / L.k;
+        if (L.k > 1) cv = (cv + 7) / 8 * 8;
+        w = (int)((cv + 64 * f.v - 1) / (64 * f.v));
+    }
     if (w > stream_max_waves(k_op, dt, f.v, f.r)) return;
     const void *fn = stream_fn(k_op, dt, f.v, f.r, L.k > 1, full);
     if (!fn) return;
@@ -572,6 +605,7 @@ void resolve_stream(credit_handle_t h, int k_op, int dt, int64_t M, int64_t N, L
         }
     }
     L.stream = true;
+    L.chunk = cv * epv;
     L.fn = fn;
     L.vpt = f.v;
     L.rows = f.r;
@@ -1286,7 +1320,7 @@ int bytes_rank(int c) { return c == 0 ? CREDIT_NUM_PLANS : c; }
 // 16384 FP32 93.8 resident, 95.8 at k = 2), so a call without a plan takes the
 // fixed rule's.
 bool stream_default(credit_handle_t h, int k_op, int dt, int64_t M, int64_t N) {
-    if (!core_op(k_op)) return false;
+    if (!core_op(k_op) && !softmax_stream(k_op)) return false;
     Launch L;
     return resolve(h, k_op, dt, M, N, fixed_rule(h, k_op, dt, M, N), false, L) == CREDIT_OK && L.stream;
 }

@@ -1,0 +1,17 @@
+// Instances of the streaming kernel: softmax backward from the logits.
+#include "stream_softmax.h"
+
+namespace credit {
+
+#define CREDIT_K(DT, V, R, SPLIT) \
+    (full ? (const void *)&k_stream_softmax<OP_SMXL_BWD, DT, V, R, SPLIT, true> : (const void *)&k_stream_softmax<OP_SMXL_BWD, DT, V, R, SPLIT, false>)
+#define CREDIT_S(DT, V, R) \
+    if (dt == DT && v == V && r == R) return split ? CREDIT_K(DT, V, R, true) : CREDIT_K(DT, V, R, false);
+
+const void *stream_kernel_smxl_bwd(int dt, int v, int r, bool split, bool full) {
+    CREDIT_S(DT_F32, 1, 2) CREDIT_S(DT_F32, 2, 2) CREDIT_S(DT_F32, 4, 1)
+    CREDIT_S(DT_BF16, 1, 2) CREDIT_S(DT_BF16, 2, 2) CREDIT_S(DT_BF16, 4, 1)
+    return nullptr;
+}
+
+}  // namespace credit
