@@ -452,7 +452,15 @@ __device__ __forceinline__ void stream_rows(const RowArgs &a, int c, int grp, St
             if constexpr (NCP > 0) { sm[i] = OP == OP_LN_BWD ? nsm[i] : 0.f; sr[i] = nsr[i]; }
         }
         const int64_t nrow = row0 + step;
-        issue(nrow < a.M ? nrow : row0, nrow < a.M ? 0xffffffffu : 0u);
+        // The wave that polls the exchange may issue its loads after it: loads
+        // return in order, and its polls would wait for them.  Only the longest
+        // rounds leave those loads time to arrive (LayerNorm backward, 4 rows of 2
+        // BF16 vectors, 2048 x 131072 k = 16: 343 -> 327 us; LayerNorm forward k = 8
+        // 198 against 211, RMSNorm backward k = 16 313 against 338).
+        constexpr bool LATE = SPLIT && OP == OP_LN_BWD && V == 2 && R == 4;
+        const bool poller = LATE && T > 64 && __builtin_amdgcn_readfirstlane(tid >> 6) == 0;
+        auto next = [&]() { issue(nrow < a.M ? nrow : row0, nrow < a.M ? 0xffffffffu : 0u); };
+        if (!poller) next();
         __builtin_amdgcn_sched_barrier(0);
         const int nr = (int)(a.M - row0 < R ? a.M - row0 : R);
 #pragma unroll
@@ -523,6 +531,8 @@ __device__ __forceinline__ void stream_rows(const RowArgs &a, int c, int grp, St
                 }
             }
             stream_reduce<OP, R, SPLIT>(st, a, row0, nr, c, lds, parity);
+            if constexpr (LATE)
+                if (poller) next();
             fresh();
 #pragma unroll
             for (int i = 0; i < R; ++i) {
@@ -594,6 +604,8 @@ __device__ __forceinline__ void stream_rows(const RowArgs &a, int c, int grp, St
                 }
             }
             stream_reduce<OP, R, SPLIT>(st, a, row0, nr, c, lds, parity);
+            if constexpr (LATE)
+                if (poller) next();
             fresh();
 #pragma unroll
             for (int i = 0; i < R; ++i) {
