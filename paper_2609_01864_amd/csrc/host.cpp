@@ -25,6 +25,7 @@ const void *multirow_kernel(int, int, int, int);
 const void *stream_kernel_bwd(int, int, int, int, bool, bool);
 const void *stream_kernel_ln_fwd(int, int, int, bool, bool);
 const void *stream_kernel_rms_fwd(int, int, int, bool, bool);
+const void *stream_kernel_ln_fp8(bool, bool);
 const void *stream_kernel_softmax(int, int, int, bool, bool);
 const void *stream_kernel_smxl_bwd(int, int, int, bool, bool);
 const void *resident_kernel_rms_fwd(int, int);
@@ -435,7 +436,8 @@ const void *stream_fn(int k_op, int dt, int v, int r, bool split, bool full) {
     switch (k_op) {
     case OP_LN_BWD:
     case OP_RMS_BWD: return stream_kernel_bwd(k_op, dt, v, r, split, full);
-    case OP_LN_FWD: return stream_kernel_ln_fwd(dt, v, r, split, full);
+    case OP_LN_FWD:
+        return dt == CREDIT_FP8_E4M3 ? stream_kernel_ln_fp8(split, full) : stream_kernel_ln_fwd(dt, v, r, split, full);
     case OP_RMS_FWD: return stream_kernel_rms_fwd(dt, v, r, split, full);
     case OP_SOFTMAX_FWD: return stream_kernel_softmax(dt, v, r, split, full);
     case OP_SMXL_BWD: return stream_kernel_smxl_bwd(dt, v, r, split, full);
@@ -547,14 +549,23 @@ StreamForm stream_form_softmax(int k_op, int dt, int k, int64_t cvec, bool lines
 // 8.3; 512 rows of 2048 are even), and of a split one a full round for every row
 // group (backward) or more than two (BF16 softmax backward from the logits 300 x
 // 32768 k = 8, two rounds: 18.5 against 23).
+//
+// FP8 LayerNorm forward (stream_fp8.h): slices of up to 1024 vectors, one a
+// lane, 4 rows a round, at every split factor (us): 4096 x 16384 52.6 -> 32.7, 4096 x
+// 65536 k = 4 247 -> 146 (k = 2, whose slices are too long: 219), 1024 x 262144 k = 16
+// 308 -> 166 (k = 8: 244), 2000 x 30000 k = 2 68 -> 50, 1500 x 100001 k = 8 220 -> 135; split
+// from more than three rounds on (1200 x 16400 k = 2, 2.3 rounds: 30.4 against 29.5
+// resident).
 void resolve_stream(credit_handle_t h, int k_op, int dt, int64_t M, int64_t N, Launch &L) {
     const int epv = dt_epv(dt);
-    if (dt == CREDIT_FP8_E4M3 || N < epv) return;
+    const bool f8 = dt == CREDIT_FP8_E4M3;
+    if ((f8 && k_op != OP_LN_FWD) || N < epv) return;
     if (h->rows_opt && (k_op == OP_LN_FWD || k_op == OP_RMS_FWD)) return;
     const int64_t cvec = L.chunk / epv;
     StreamForm f;
     if (k_op == OP_LN_BWD || k_op == OP_RMS_BWD) f = stream_form_norm_bwd(k_op, dt, L.k, cvec);
-    if (k_op == OP_LN_FWD || k_op == OP_RMS_FWD)
+    if (f8) f = {1, 4, 0};  // below
+    else if (k_op == OP_LN_FWD || k_op == OP_RMS_FWD)
         f = stream_form_norm_fwd(k_op, dt, L.k, cvec, N == L.k * cvec * epv && cvec % 512 == 0, N % epv == 0);
     if (softmax_stream(k_op)) f = stream_form_softmax(k_op, dt, L.k, cvec, N % (16 * epv) == 0);
     if (!f.v) return;
@@ -568,7 +579,7 @@ void resolve_stream(credit_handle_t h, int k_op, int dt, int64_t M, int64_t N, L
         if (L.k > 1) cv = (cv + 7) / 8 * 8;
         w = (int)((cv + 64 * f.v - 1) / (64 * f.v));
     }
-    if (w > stream_max_waves(k_op, dt, f.v, f.r)) return;
+    if (w > (f8 ? kStreamWaves : stream_max_waves(k_op, dt, f.v, f.r))) return;
     const void *fn = stream_fn(k_op, dt, f.v, f.r, L.k > 1, full);
     if (!fn) return;
     int occ = occupancy(h, fn, w * 64, 0);
@@ -579,7 +590,7 @@ void resolve_stream(credit_handle_t h, int k_op, int dt, int64_t M, int64_t N, L
     const int64_t blocks = (M + f.r - 1) / f.r;
     if (gmax < 1) return;
     const bool bwd = k_op == OP_LN_BWD || k_op == OP_RMS_BWD;
-    if (L.k > 1 ? blocks < gmax || (!bwd && blocks <= 2 * gmax)
+    if (L.k > 1 ? blocks < gmax || (!bwd && blocks <= (f8 ? 3 : 2) * gmax)
                 : blocks < std::min<int64_t>(gmax, h->cus) || (f.many && blocks <= 2 * gmax))
         return;
     int64_t groups = 0;
@@ -1313,16 +1324,27 @@ credit_status_t analytic_pick(credit_handle_t h, int k_op, int dt, int64_t M, in
 // exchange traffic that grows with k), the two-pass plan rereads them.
 int bytes_rank(int c) { return c == 0 ? CREDIT_NUM_PLANS : c; }
 
-// Whether the fixed rule's plan of the shape runs in the streaming form, which
-// the network's training timings predate.  Rows are then fastest with the
+// The plan of a call without one where the streaming form, which the network's
+// training timings predate, has a better one.  Rows are then fastest with the
 // fewest members they need (BF16 LayerNorm backward 4096 x 5120: 34 us resident,
 // 46 at the network's k = 2; 4096 x 16384: 88 at k = 2 and 4, 91 at 8; forward 4096 x
-// 16384 FP32 93.8 resident, 95.8 at k = 2), so a call without a plan takes the
-// fixed rule's.
-bool stream_default(credit_handle_t h, int k_op, int dt, int64_t M, int64_t N) {
+// 16384 FP32 93.8 resident, 95.8 at k = 2): the fixed rule's plan, if it streams,
+// and for the FP8 LayerNorm forward, whose one-row kernels are slower at any k,
+// the first plan that does.
+bool stream_default(credit_handle_t h, int k_op, int dt, int64_t M, int64_t N, credit_plan_t *out) {
     if (!core_op(k_op) && !softmax_stream(k_op)) return false;
-    Launch L;
-    return resolve(h, k_op, dt, M, N, fixed_rule(h, k_op, dt, M, N), false, L) == CREDIT_OK && L.stream;
+    const bool any = k_op == OP_LN_FWD && dt == CREDIT_FP8_E4M3;
+    for (int c = 1; c < CREDIT_NUM_PLANS; ++c) {
+        const credit_plan_t p = class_plan(c);
+        if (!plan_ok(h, k_op, dt, M, N, p)) continue;
+        Launch L;
+        if (resolve(h, k_op, dt, M, N, p, false, L) == CREDIT_OK && L.stream) {
+            *out = p;
+            return true;
+        }
+        if (!any) break;  // the first legal one is the fixed rule's
+    }
+    return false;
 }
 
 // Every legal plan timed (cache flush, median of 15).  The fastest median is
@@ -1439,8 +1461,9 @@ credit_status_t pick_plan(credit_handle_t h, int k_op, int dt, int64_t M, int64_
             return CREDIT_OK;
         }
         st = CREDIT_ERR_MODEL;
-        if (sel != CREDIT_SEL_FIXED && h->has_model && core_op(k_op) && !stream_default(h, k_op, dt, M, N))
-            st = learned_pick(h, k_op, dt, M, N, false, out, pred);
+        if (sel != CREDIT_SEL_FIXED && h->has_model && core_op(k_op))
+            st = stream_default(h, k_op, dt, M, N, out) ? CREDIT_OK
+                                                        : learned_pick(h, k_op, dt, M, N, false, out, pred);
         if (st != CREDIT_OK) *out = fixed_rule(h, k_op, dt, M, N);
         h->plan_cache[key] = *out;
         return CREDIT_OK;
