@@ -530,8 +530,19 @@ StreamForm stream_form_norm_fwd(int k_op, int dt, int k, int64_t cvec, bool whol
 // over 512 vectors keep the one-row kernels where rows are whole lines (2048 x
 // 32768 k = 2 51.7 against 53.6 and 76 against 80), as do FP32 ones of the backward
 // (2048 x 50257 k = 8 224 against 232).
-StreamForm stream_form_softmax(int k_op, int dt, int k, int64_t cvec, bool lines) {
-    const bool fwd = k_op == OP_SOFTMAX_FWD;
+//
+// FP8 (forward): 4 vectors a lane, their exponentials kept, so that each is taken
+// once, where slices are whole vectors of every lane (4096 x 65536 113 -> 95, 1024 x
+// 262144 k = 4 122 -> 108) and for resident rows that end in a part of a vector (4096
+// x 17001 61 -> 51); the others gain nothing (2000 x 30000 31.9 against 31.2, 1500 x
+// 16400 20.4 against 22.6, 1500 x 100001 k = 4 96.4 against 99.9), nor do 9 to 12 waves,
+// one workgroup per CU (3000 x 33333 67.9 against 69.6).
+StreamForm stream_form_softmax(int k_op, int dt, int k, int64_t cvec, int64_t N) {
+    const bool fwd = k_op == OP_SOFTMAX_FWD, lines = N % (16 * dt_epv(dt)) == 0;
+    if (dt == CREDIT_FP8_E4M3) {
+        const bool whole = N == k * cvec * 16 && cvec % 256 == 0;
+        return cvec <= 4096 && (whole || (k == 1 && N % 16 && cvec + 9 <= 4096 && (cvec + 9 <= 2048 || cvec > 3072))) ? StreamForm{4, 1, 0} : StreamForm{};
+    }
     if (cvec <= (fwd || k == 1 ? 64 : 640)) return {1, 2, 0};
     if (cvec <= 512) return {2, 2, 0};
     if (k > 1 && (lines || (dt == CREDIT_F32 && !fwd))) return {};
@@ -559,15 +570,15 @@ StreamForm stream_form_softmax(int k_op, int dt, int k, int64_t cvec, bool lines
 void resolve_stream(credit_handle_t h, int k_op, int dt, int64_t M, int64_t N, Launch &L) {
     const int epv = dt_epv(dt);
     const bool f8 = dt == CREDIT_FP8_E4M3;
-    if ((f8 && k_op != OP_LN_FWD) || N < epv) return;
+    if ((f8 && k_op != OP_LN_FWD && k_op != OP_SOFTMAX_FWD) || N < epv) return;
     if (h->rows_opt && (k_op == OP_LN_FWD || k_op == OP_RMS_FWD)) return;
     const int64_t cvec = L.chunk / epv;
     StreamForm f;
     if (k_op == OP_LN_BWD || k_op == OP_RMS_BWD) f = stream_form_norm_bwd(k_op, dt, L.k, cvec);
-    if (f8) f = {1, 4, 0};  // below
+    if (f8 && k_op == OP_LN_FWD) f = {1, 4, 0};  // above
     else if (k_op == OP_LN_FWD || k_op == OP_RMS_FWD)
         f = stream_form_norm_fwd(k_op, dt, L.k, cvec, N == L.k * cvec * epv && cvec % 512 == 0, N % epv == 0);
-    if (softmax_stream(k_op)) f = stream_form_softmax(k_op, dt, L.k, cvec, N % (16 * epv) == 0);
+    else if (softmax_stream(k_op)) f = stream_form_softmax(k_op, dt, L.k, cvec, N);
     if (!f.v) return;
     // vectors of a slice: the softmax family's rows begin up to 126 bytes into
     // their first line (stream_softmax.h), and its slices are whole lines
@@ -603,7 +614,11 @@ void resolve_stream(credit_handle_t h, int k_op, int dt, int64_t M, int64_t N, L
         // Of all groups that finish in the same number of rounds the fewest;
         // and of those numbers of workgroups per CU, down to half of what fits,
         // the one that leaves the busiest CU the fewest rounds (1366 groups of 3
-        // rounds are 5.3 per CU, so some CUs work 18 rounds; 1024 of 4 work 16).
+        // rounds are 5.3 per CU, so some CUs work 18 rounds; 1024 of 4 work 16)
+        // -- or, where that is fewer still, as many groups as fit, some with a
+        // round more than others (FP8 softmax of 1165 rows, 5 waves each:
+        // 583 groups of 2 rounds 22.9 us, 768 groups 19.1; FP32 LayerNorm 4095 x 5003, a tie: 31.8
+        // against 34.5).
         int64_t least = INT64_MAX;
         for (int p = occ; p >= (occ + 1) / 2; --p) {
             const int64_t g = std::min<int64_t>(gmax, (int64_t)p * h->cus);
@@ -614,6 +629,10 @@ void resolve_stream(credit_handle_t h, int k_op, int dt, int64_t M, int64_t N, L
                 groups = n;
             }
         }
+        const int64_t all = std::min(gmax, blocks);
+        int64_t busiest = 0;  // CU 0 has the first of every h->cus groups
+        for (int64_t w = 0; w < all; w += h->cus) busiest += (blocks - w + all - 1) / all;
+        if (!ncp_of(k_op) && busiest < least) groups = all;
     }
     L.stream = true;
     L.chunk = cv * epv;

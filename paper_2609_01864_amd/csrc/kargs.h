@@ -111,7 +111,7 @@ constexpr int stream_params(int op) { return op == OP_LN_FWD ? 2 : (op == OP_RMS
 constexpr int stream_ncp(int op) { return op == OP_LN_BWD ? 2 : op == OP_RMS_BWD ? 1 : 0; }
 // Registers a lane needs: two buffers of R rows, parameters, column sums.
 constexpr int stream_regs(int op, int dt, int v, int r) {
-    const int epv = dt == DT_F32 ? 4 : 8;
+    const int epv = dt == DT_F32 ? 4 : dt == DT_BF16 ? 8 : 16;
     return 2 * r * v * 4 * (two_in(op) ? 2 : 1) + v * epv * (stream_params(op) + stream_ncp(op)) + 48;
 }
 // Most waves of a workgroup: its registers have to fit the CU's 4 x 512.

@@ -17,7 +17,7 @@ namespace credit {
 template <int OP, int DT, int V, int R, bool FULL, bool SPLIT>
 __device__ __forceinline__ void stream_softmax_rows(const RowArgs &a, int c, int grp, StreamLds<OP, R> &lds) {
     constexpr int EPV = Io<DT>::EPV, B = Io<DT>::BYTES;
-    constexpr bool TWO = two_in(OP);
+    constexpr bool TWO = two_in(OP), FP8 = DT == DT_FP8;
     typedef StreamStat<OP> S;
     const int tid = threadIdx.x, T = (int)blockDim.x;
     int parity = 0;
@@ -48,6 +48,7 @@ __device__ __forceinline__ void stream_softmax_rows(const RowArgs &a, int c, int
 
     u32x4 x0[R][V], x1[TWO ? R : 1][TWO ? V : 1];
     u32x4 n0[R][V], n1[TWO ? R : 1][TWO ? V : 1];
+    float xs[R], nxs[R];  // input scales (FP8)
     // Loads of the round at row0; `live` as in stream.h.
     auto issue = [&](int64_t row0, uint32_t live) {
         uint32_t lb = (uint32_t)lane0 & live;
@@ -57,6 +58,7 @@ __device__ __forceinline__ void stream_softmax_rows(const RowArgs &a, int c, int
             const int64_t row = row0 + i < a.M ? row0 + i : row0;
             const char *r0 = (const char *)a.in0 + row * a.ld0 * B;
             const char *r1 = TWO ? (const char *)a.in1 + row * a.ld1 * B : nullptr;
+            if constexpr (FP8) nxs[i] = a.s0[row];
             if constexpr (FULL) {
 #pragma unroll
                 for (int j = 0; j < V; ++j) n0[i][j] = vload_nt<false>(r0 + ((uint32_t)(j * T) * 16u & live), lb);
@@ -81,13 +83,18 @@ __device__ __forceinline__ void stream_softmax_rows(const RowArgs &a, int c, int
             }
         }
     };
-    // `fill` into the elements of a slot that are not its own
+    // which elements of a slot are the lane's own (bytes [lo, hi) of the vector)
+    auto bounds = [&](int j, int h, int &lo, int &hi) {
+        const int o = at(j, h);
+        lo = o > rowlast ? o - rowlast : 0;
+        hi = SPLIT && j * T >= inside ? 0 : o < 0 ? o + 16 : 16;
+    };
+    // `fill` into the elements that are not
     auto mask = [&](u32x4 &d, int j, int h, unsigned fill) {
         if constexpr (!FULL) {
             if (__builtin_amdgcn_ballot_w64(whole(j, h)) == ~0ull) return;
-            const int o = at(j, h);
-            const int lo = o > rowlast ? o - rowlast : 0;
-            const int hi = SPLIT && j * T >= inside ? 0 : o < 0 ? o + 16 : 16;
+            int lo, hi;
+            bounds(j, h, lo, hi);
 #pragma unroll
             for (int w = 0; w < 4; ++w) {
                 unsigned m;
@@ -115,13 +122,14 @@ __device__ __forceinline__ void stream_softmax_rows(const RowArgs &a, int c, int
             const bool ok = o >= 0 && o <= rowlast && (!SPLIT || j * T < inside);
             __builtin_amdgcn_raw_buffer_store_b128(v, rs, ok ? (uint32_t)o : 0x80000000u, 0, CREDIT_STORE_NT ? 2 : 0);
             if (__builtin_amdgcn_ballot_w64(ok) != ~0ull && live && !ok) {
-                const int lo = o > rowlast ? o - rowlast : 0;
-                const int hi = SPLIT && j * T >= inside ? 0 : o < 0 ? o + 16 : 16;
+                int lo, hi;
+                bounds(j, h, lo, hi);
                 char *p = orow + held(o);
 #pragma unroll
                 for (int i = 0; i < EPV; ++i) {
                     if (i * B < lo || i * B >= hi) continue;
                     if constexpr (B == 4) *(unsigned *)(p + i * B) = v[i];
+                    else if constexpr (B == 1) p[i] = (char)(v[i / 4] >> (8 * (i & 3)));
                     else *(unsigned short *)(p + i * B) = (unsigned short)(v[i / 2] >> (16 * (i & 1)));
                 }
             }
@@ -140,6 +148,7 @@ __device__ __forceinline__ void stream_softmax_rows(const RowArgs &a, int c, int
                 x0[i][j] = n0[i][j];
                 if constexpr (TWO) x1[i][j] = n1[i][j];
             }
+            xs[i] = FP8 ? nxs[i] : 1.f;
         }
         const int64_t nrow = row0 + step;
         issue(nrow < a.M ? nrow : row0, nrow < a.M ? 0xffffffffu : 0u);
@@ -160,41 +169,55 @@ __device__ __forceinline__ void stream_softmax_rows(const RowArgs &a, int c, int
         };
         // Exponentials about the wave's maximum c in base-2 units, rounded up to
         // a whole number: 32 - c and the factors 2^(c - c') by which the sums of
-        // the waves (and members) are rescaled when merged are then exact.  It is
-        // held finite unless it is -inf itself: rows masked with the type's
+        // the waves (and members) are rescaled when merged are then exact (FP8
+        // takes it as it is: its largest code, 448, stands for 2^0).  It is held
+        // finite unless it is -inf itself: rows masked with the type's
         // lowest value would else add inf * 0.  Elements that are not the lane's
         // own are -inf (and their dy 0), so they add nothing.
         //
         // KEEP: the exponentials stay in registers for the output (the exponential
-        // is the dearest instruction here: 2048 x 50257 BF16 k = 4 98 -> 91 us, FP32
-        // outputs keep their last bits); short BF16 rows run faster with more
+        // is the dearest instruction here: 2048 x 50257 BF16 k = 4 98 -> 91 us, FP8 4096
+        // x 65536 113 -> 95, FP32 outputs keep their last bits); short BF16 rows run faster with more
         // workgroups (16384 x 1000: 14.9 against 15.7) and the widest slices have no
         // registers for them.  Kept BF16 exponentials, and FP32 ones of the
         // backward, are 2^(v + 32), so that results down to 2^-158 of the largest
         // keep their value (device.h).
         constexpr bool BW = OP == OP_SMXL_BWD, KEEP = V == 4 || (DT == DT_F32 && !BW);
-        constexpr float SH = KEEP && (DT != DT_F32 || BW) ? kExpShift : 0.f;
+        constexpr float SH = KEEP && (DT == DT_BF16 || BW) ? kExpShift : 0.f;
         constexpr float USH = SH == 0.f ? 1.f : kExpUnshift;
         constexpr unsigned NINF = DT == DT_F32 ? 0xff800000u : 0xff80ff80u;
         float st[R][S::NS], ct[R];
         float ev[KEEP ? R : 1][KEEP ? V * EPV : 1];
 #pragma unroll
         for (int i = 0; i < R; ++i) {
+            const float K = xs[i] * kLog2e;
             float qmax = -INFINITY;
 #pragma unroll
             for (int j = 0; j < V; ++j) {
                 if (empty(j, ph[i])) continue;
-                mask(x0[i][j], j, ph[i], NINF);
-                if constexpr (BW) mask(x1[i][j], j, ph[i], 0u);
                 float q[EPV];
-                decode<DT>(x0[i][j], q, 1.f);
+                if constexpr (FP8) {
+                    // (e4m3 has no infinity to mask with)
+                    decode<DT>(x0[i][j], q, 1.f);
+                    if (!FULL && __builtin_amdgcn_ballot_w64(whole(j, ph[i])) != ~0ull) {
+                        int lo, hi;
+                        bounds(j, ph[i], lo, hi);
+#pragma unroll
+                        for (int e = 0; e < EPV; ++e) q[e] = e >= lo && e < hi ? q[e] : -INFINITY;
+                    }
+                } else {
+                    mask(x0[i][j], j, ph[i], NINF);
+                    if constexpr (BW) mask(x1[i][j], j, ph[i], 0u);
+                    decode<DT>(x0[i][j], q, 1.f);
+                }
 #pragma unroll
                 for (int e = 0; e < EPV; ++e) qmax = fmaxf(qmax, q[e]);
                 keep_order(qmax);
             }
             opaque<V>(x0[i]);
             qmax = wave_max(qmax);
-            st[i][0] = qmax == -INFINITY ? -INFINITY : fmaxf(ceilf(qmax * kLog2e), -0x1.fffffep+127f);
+            const float cm = FP8 ? qmax * K : ceilf(qmax * kLog2e);
+            st[i][0] = qmax == -INFINITY ? -INFINITY : fmaxf(cm, -0x1.fffffep+127f);
             ct[i] = qmax == -INFINITY ? 0.f : st[i][0];
             const float cs = SH - ct[i];
             float s = 0.f, t = 0.f;
@@ -204,9 +227,17 @@ __device__ __forceinline__ void stream_softmax_rows(const RowArgs &a, int c, int
                 float q[EPV], g[EPV];
                 decode<DT>(x0[i][j], q, 1.f);
                 if constexpr (BW) decode<DT>(x1[i][j], g, 1.f);
+                if constexpr (FP8 && !FULL) {
+                    if (__builtin_amdgcn_ballot_w64(whole(j, ph[i])) != ~0ull) {
+                        int lo, hi;
+                        bounds(j, ph[i], lo, hi);
+#pragma unroll
+                        for (int e = 0; e < EPV; ++e) q[e] = e >= lo && e < hi ? q[e] : -INFINITY;
+                    }
+                }
 #pragma unroll
                 for (int e = 0; e < EPV; ++e) {
-                    const float x = fast_exp2(fmaf(q[e], kLog2e, cs));
+                    const float x = fast_exp2(fmaf(q[e], FP8 ? K : kLog2e, cs));
                     s += x;
                     if constexpr (BW) t = fmaf(x, g[e], t);
                     if constexpr (KEEP) ev[i][j * EPV + e] = x;
@@ -229,7 +260,11 @@ __device__ __forceinline__ void stream_softmax_rows(const RowArgs &a, int c, int
             const float cdot = BW ? st[i][S::NS - 1] * inv_s : 0.f;
             float f = mul;
             // the clamps keep 0 times the factor 0 for a wave without a finite element
-            if constexpr (KEEP && SH == 0.f) {
+            if constexpr (FP8) {
+                // the largest output is 2^0 / s: the codes are 448 2^(v - c)
+                f = fast_exp2(fminf(ct[i] - cmax, 64.f)) * kFp8Max;
+                if (c == 0 && tid == 0 && i < nr) a.so[row0 + i] = inv_s / kFp8Max;
+            } else if constexpr (KEEP && SH == 0.f) {
                 f = fast_exp2(fminf(ct[i] - cmax, 64.f)) * inv_s;
             } else if constexpr (KEEP) {
                 // y = e 2^(ct - c + 32) 2^-64 / s.  A wave whose maximum lies far

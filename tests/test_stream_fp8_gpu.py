@@ -1,8 +1,8 @@
-"""The streaming form of the FP8 LayerNorm forward at the sizes where its slices
-end -- one vector, whole waves, one vector more, the largest, partial vectors,
-short and empty members, a last round with fewer rows -- against the oracle, its
-plan when none is given, and rows whose spread is far below their mean, that
-are constant or hold a NaN code."""
+"""The streaming forms of the FP8 LayerNorm and softmax forward at the sizes where
+their slices end -- one vector, whole waves, one vector more, the largest,
+partial vectors, short and empty members, a last round with fewer rows --
+against the oracle, the LayerNorm's plan when none is given, and rows whose
+spread is far below their mean, that are constant or hold a NaN code."""
 import numpy as np
 import pytest
 import torch
@@ -123,3 +123,42 @@ def test_plan_of_a_call_without_one(capped):
         assert h.check_errors() == C.OK
     finally:
         h.close()
+
+
+@pytest.mark.gpu
+@pytest.mark.parametrize("k", [1, 2, 8])
+def test_softmax_slice_edges_and_phases(capped, k):
+    p = C.plan("split", k) if k > 1 else C.plan("resident")
+    vecs = (1, 2, 64, 65, 255, 256, 257, 1000, 4087, 4096) if k == 1 else (256, 512, 4096) if k == 2 else (256, 1024)
+    seen = 0
+    for n, vec in enumerate(vecs):
+        full = vec * k * 16
+        for N in {full, full - 1, full - 15} if k == 1 else {full}:
+            if not capped.plan_legal(*OPNUM["softmax_fwd"], C.FP8, 7, N, p):
+                continue
+            g = capped.geometry(*OPNUM["softmax_fwd"], C.FP8, 7, N, p)
+            one = C.plan_geometry(None, *OPNUM["softmax_fwd"], C.FP8, 7, N, p)
+            seen += g["block"] != one["block"] or g["vpt"] != one["vpt"]
+            print(f"[stream] fp8 softmax 7 x {N} {p} {g}", flush=True)
+            case = Case("softmax_fwd", "fp8", 7, N, seed=n + N)
+            ref = case.reference()
+            check_case(case, case.run(capped, p, ref=ref), ref)
+            for pad, off in ((0, 1), (5, 0), (77, 13), (128, 128)):
+                check_case(case, case.run(capped, p, ld_pad=pad, offset=off, ref=ref), ref)
+    assert seen >= 1  # (slices of 1024 vectors have the one-row kernels' geometry)
+    assert capped.check_errors() == C.OK
+
+
+@pytest.mark.gpu
+def test_softmax_nan_row(capped):
+    q = (torch.randn((9, 20001), device="cuda") * 50).to(torch.float8_e4m3fn)
+    s = torch.rand(9, device="cuda") * 1e-2 + 1e-3
+    y, ys = C.softmax_fwd(q, s, p=C.plan("resident"), h=capped)
+    bad = q.clone()
+    bad.view(torch.uint8)[4, 777] = 0x7F
+    print("[stream] fp8 softmax nan", flush=True)
+    z, zs = C.softmax_fwd(bad, s, p=C.plan("resident"), h=capped)
+    keep = [i for i in range(9) if i != 4]
+    assert bool(torch.isnan(zs[4])) and torch.equal(zs[keep], ys[keep])
+    assert torch.equal(z.view(torch.uint8)[keep], y.view(torch.uint8)[keep])
+    assert capped.check_errors() == C.OK
