@@ -26,6 +26,7 @@ const void *stream_kernel_bwd(int, int, int, int, bool, bool);
 const void *stream_kernel_ln_fwd(int, int, int, bool, bool);
 const void *stream_kernel_rms_fwd(int, int, int, bool, bool);
 const void *stream_kernel_ln_fp8(bool, bool);
+const void *stream_kernel_quant(int, int, int, bool, bool);
 const void *stream_kernel_softmax(int, int, int, bool, bool);
 const void *stream_kernel_smxl_bwd(int, int, int, bool, bool);
 const void *resident_kernel_rms_fwd(int, int);
@@ -440,6 +441,7 @@ const void *stream_fn(int k_op, int dt, int v, int r, bool split, bool full) {
         return dt == CREDIT_FP8_E4M3 ? stream_kernel_ln_fp8(split, full) : stream_kernel_ln_fwd(dt, v, r, split, full);
     case OP_RMS_FWD: return stream_kernel_rms_fwd(dt, v, r, split, full);
     case OP_SOFTMAX_FWD: return stream_kernel_softmax(dt, v, r, split, full);
+    case OP_QUANT_I8: return stream_kernel_quant(dt, v, r, split, full);
     case OP_SMXL_BWD: return stream_kernel_smxl_bwd(dt, v, r, split, full);
     default: return nullptr;
     }
@@ -552,6 +554,25 @@ StreamForm stream_form_softmax(int k_op, int dt, int k, int64_t cvec, int64_t N)
     return {};
 }
 
+// Row-wise int8 quantisation (stream_quant.h), as above (us, inputs from HBM): BF16
+// 4096 x 11008 41.7 -> 25, 8192 x 2048 18 -> 10.9, ragged 3000 x 11001 37 -> 21, 2048 x
+// 20480 41 -> 22, 1024 x 65536 67 -> 36, k = 4 44 -> 41, k = 8 53 -> 44; FP32 4096 x 4096
+// 17.5 -> 15.8, 2048 x 28672 57 -> 50, 4096 x 4096 k = 2 29 -> 23.  FP32 slices of split
+// rows over 1024 vectors keep the one-row kernel (2048 x 28672 k = 2 56 against 61, k
+// = 4 59.4 against 60.2).
+StreamForm stream_form_quant(int dt, int k, int64_t cvec) {
+    if (cvec <= 64) return {1, 2, 0};
+    if (k == 1) {
+        if (cvec <= 2048) return {2, 2, 0};
+        if (cvec <= 4096) return {4, 1, 0};
+        if (cvec <= 8192) return {8, 1, 0};
+        return {};
+    }
+    if (cvec <= 640 || (dt == CREDIT_F32 && cvec <= 1024)) return {2, 2, 0};
+    if (dt != CREDIT_F32 && cvec <= 4096) return {4, 1, 0};
+    return {};
+}
+
 // Replaces a resident / split plan's kernel by the streaming one where that is
 // faster: FP32 / BF16 rows of at least one vector, and enough rows -- a workgroup
 // for every CU of a row-resident plan (its waves work alone or in small groups,
@@ -578,6 +599,7 @@ void resolve_stream(credit_handle_t h, int k_op, int dt, int64_t M, int64_t N, L
     if (f8 && k_op == OP_LN_FWD) f = {1, 4, 0};  // above
     else if (k_op == OP_LN_FWD || k_op == OP_RMS_FWD)
         f = stream_form_norm_fwd(k_op, dt, L.k, cvec, N == L.k * cvec * epv && cvec % 512 == 0, N % epv == 0);
+    else if (k_op == OP_QUANT_I8) f = stream_form_quant(dt, L.k, cvec);
     else if (softmax_stream(k_op)) f = stream_form_softmax(k_op, dt, L.k, cvec, N);
     if (!f.v) return;
     // vectors of a slice: the softmax family's rows begin up to 126 bytes into
@@ -590,7 +612,7 @@ void resolve_stream(credit_handle_t h, int k_op, int dt, int64_t M, int64_t N, L
         if (L.k > 1) cv = (cv + 7) / 8 * 8;
         w = (int)((cv + 64 * f.v - 1) / (64 * f.v));
     }
-    if (w > (f8 ? kStreamWaves : stream_max_waves(k_op, dt, f.v, f.r))) return;
+    if (w > (f8 || k_op == OP_QUANT_I8 ? kStreamWaves : stream_max_waves(k_op, dt, f.v, f.r))) return;
     const void *fn = stream_fn(k_op, dt, f.v, f.r, L.k > 1, full);
     if (!fn) return;
     int occ = occupancy(h, fn, w * 64, 0);
