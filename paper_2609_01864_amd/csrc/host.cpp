@@ -583,11 +583,11 @@ StreamForm stream_form_quant(int dt, int k, int64_t cvec) {
 // 32768 k = 8, two rounds: 18.5 against 23).
 //
 // FP8 LayerNorm forward (stream_fp8.h): slices of up to 1024 vectors, one a
-// lane, 4 rows a round, at every split factor (us): 4096 x 16384 52.6 -> 32.7, 4096 x
-// 65536 k = 4 247 -> 146 (k = 2, whose slices are too long: 219), 1024 x 262144 k = 16
-// 308 -> 166 (k = 8: 244), 2000 x 30000 k = 2 68 -> 50, 1500 x 100001 k = 8 220 -> 135; split
-// from more than three rounds on (1200 x 16400 k = 2, 2.3 rounds: 30.4 against 29.5
-// resident).
+// lane, 4 rows a round, at every split factor (us): 4096 x 16384 52.6 -> 32.4, 4096 x
+// 65536 k = 8 328 -> 137 (k = 2, whose slices are too long: 219), 1024 x 262144 k = 16
+// 308 -> 151 (k = 8: 244), 2000 x 30000 k = 2 68 -> 47, 1500 x 100001 k = 16 306 -> 114;
+// split from more than three rounds on (1200 x 16400 k = 2, 2.3 rounds: 30.4 against
+// 29.5 resident).
 void resolve_stream(credit_handle_t h, int k_op, int dt, int64_t M, int64_t N, Launch &L) {
     const int epv = dt_epv(dt);
     const bool f8 = dt == CREDIT_FP8_E4M3;
@@ -1371,21 +1371,27 @@ int bytes_rank(int c) { return c == 0 ? CREDIT_NUM_PLANS : c; }
 // 46 at the network's k = 2; 4096 x 16384: 88 at k = 2 and 4, 91 at 8; forward 4096 x
 // 16384 FP32 93.8 resident, 95.8 at k = 2): the fixed rule's plan, if it streams,
 // and for the FP8 LayerNorm forward, whose one-row kernels are slower at any k,
-// the first plan that does.
+// the first plan that does -- the second where the first leaves one workgroup of
+// 13 to 16 waves per CU, whose barriers nothing hides (4096 x 65536 143 at k = 4, 137
+// at 8; 1500 x 100001 126 at 8, 114 at 16; 1024 x 262144 151 at 16, 146 at 32; shorter
+// rows would gain nothing: 2000 x 30000 47 at 2, 49.5 at 4).
 bool stream_default(credit_handle_t h, int k_op, int dt, int64_t M, int64_t N, credit_plan_t *out) {
     if (!core_op(k_op) && !softmax_stream(k_op)) return false;
     const bool any = k_op == OP_LN_FWD && dt == CREDIT_FP8_E4M3;
+    bool found = false;
     for (int c = 1; c < CREDIT_NUM_PLANS; ++c) {
         const credit_plan_t p = class_plan(c);
         if (!plan_ok(h, k_op, dt, M, N, p)) continue;
         Launch L;
         if (resolve(h, k_op, dt, M, N, p, false, L) == CREDIT_OK && L.stream) {
             *out = p;
-            return true;
+            if (found || !any || N < 32768 || L.block <= 768) return true;
+            found = true;
+        } else if (!any) {
+            break;  // the first legal one is the fixed rule's
         }
-        if (!any) break;  // the first legal one is the fixed rule's
     }
-    return false;
+    return found;
 }
 
 // Every legal plan timed (cache flush, median of 15).  The fastest median is

@@ -4,20 +4,24 @@
 // twice per row: 4096 x 65536 moved 4.3 GB through the L2s for 0.5 GB of HBM
 // traffic and took 2.6 times as long as the latter (220 us for 83).  Here a lane
 // holds one vector (16 elements) of a slice with its gamma / beta in registers
-// for all its rows, a round is 4 rows, and the next round's loads are in flight:
-// 146 us with k = 4.
+// for all its rows, a round is 4 rows, and later rounds' loads are in flight:
+// 137 us with k = 8.
 //
-// The statistics of a round's rows are reduced for all of them at once: a wave
-// folds its 4 registers into one, lane group ri (16 lanes) holding row ri, so that merging waves, polling the members of a split row, the reciprocal
-// square root and the output scale are one instruction for 4 rows.
+// The statistics (mean and M2, then the largest output) of the rows are reduced
+// for 4 rows at once: a wave folds its 4 registers into one, lane group ri (16
+// lanes) holding row ri, so that merging waves, polling the members of a split
+// row, the reciprocal square root and the output scale are one instruction for
+// 4 rows.  On split rows the statistics of the next round travel with the
+// largest output of this one, and the round before is written while they do:
+// one exchange per round, none of it waited for (two, in sequence: 146 us with k
+// = 4, 118 without waiting for the polls; 1024 x 262144 k
+// = 16 166 -> 151).
 //
-// Bound: arithmetic, 12 instructions an element (90 of the 146 us: the output is
-// evaluated once for its maximum and once to be written), and the two exchanges
-// of a round (28 us).  More does not fit: the outputs kept between the two take
-// 64 registers of the 128 that 16 waves leave a lane (177-187 us with 8), 8 rows
-// a round spill (153), and moving the next round's statistics into the exchange
-// of this one's maximum, with three sets of rows, spills as well (143-147; 35
-// against 33 us where nothing is exchanged, 4096 x 16384).
+// Bound: arithmetic, 12 instructions an element (90 of the 137 us: the output is
+// evaluated once for its maximum and once to be written), and the next rows'
+// loads, which have registers only from the moment the rows before are written.
+// More does not fit: the outputs kept between the two take 64 registers of the
+// 128 that 16 waves leave a lane (177-187 us with 8 waves), 8 rows a round spill.
 #pragma once
 #include "stream.h"
 
@@ -64,43 +68,49 @@ template <class F> __device__ __forceinline__ float fold(const float (&v)[kF8Row
     return c[0];
 }
 
-// (count, mean, M2) or a single maximum, in lane groups: merge rules.
-struct MergeMax1 {
-    __device__ __forceinline__ void operator()(float (&a)[1], const float (&b)[1]) const { a[0] = fmaxf(a[0], b[0]); }
+// (count, mean, M2) and a maximum.
+struct MergeChanMax {
+    __device__ __forceinline__ void operator()(float (&a)[4], const float (&b)[4]) const {
+        float x[3] = {a[0], a[1], a[2]};
+        const float y[3] = {b[0], b[1], b[2]};
+        MergeChanSel()(x, y);
+        a[0] = x[0]; a[1] = x[1]; a[2] = x[2];
+        a[3] = fmaxf(a[3], b[3]);
+    }
 };
 
 struct StreamF8Lds {
-    float red[2][kStreamWaves][kF8Rows][3];
-    float xb[kF8Rows][3];
+    float red[2][kStreamWaves][kF8Rows][4];
+    float xb[kF8Rows][4];
 };
 
-// Merges the waves' (and members') tuples of the rows, one row per lane group;
-// STAGE 0: (count, mean, M2), the count of a member following from its slice;
-// STAGE 1: the largest output.  As stream_reduce otherwise.
-template <bool SPLIT, int STAGE, int NS, class Merge>
-__device__ __forceinline__ void f8_reduce(float (&v)[NS], Merge merge, const RowArgs &a, int64_t row0, int nr, int c,
-                                          StreamF8Lds &lds, int &parity) {
-    constexpr int G = kF8Group, NX = STAGE == 0 ? 2 : 1;
+// Merges the waves' tuples, row i of the rounds in lane group i: (count, mean,
+// M2) of the `ns` rows at `srow`, and the largest output of the `na` rows at `arow`.
+// Row-resident: every wave gets the merged tuples.  Split: wave 0 does, and
+// publishes them; f8_gather returns those of the row group.
+template <bool SPLIT>
+__device__ __forceinline__ void f8_publish(float (&v)[4], const RowArgs &a, int64_t srow, int ns, int64_t arow, int na,
+                                           int c, StreamF8Lds &lds, int &parity) {
+    constexpr int G = kF8Group;
+    const MergeChanMax merge;
     const int lane = threadIdx.x & 63, wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
     const int nw = __builtin_amdgcn_readfirstlane(blockDim.x >> 6);
     const int ri = fold_row(lane), p = lane & (G - 1);
     if (nw > 1) {
-        float(*red)[kF8Rows][3] = lds.red[parity];
-        if (p == 0) {
-#pragma unroll
-            for (int s = 0; s < NS; ++s) red[wave][ri][s] = v[s];
-        }
+        float(*red)[kF8Rows][4] = lds.red[parity];
+        if (p == 0) *(f32x4 *)red[wave][ri] = f32x4{v[0], v[1], v[2], v[3]};
         lds_barrier();
         parity ^= 1;
         if (!SPLIT || wave == 0) {
 #pragma unroll
             for (int h = 0; h < kStreamWaves / G; ++h) {
-                float o[NS];
-#pragma unroll
-                for (int s = 0; s < NS; ++s) o[s] = p + G * h < nw ? red[p + G * h][ri][s] : 0.f;
+                const int w = p + G * h;
+                f32x4 u = {0.f, 0.f, 0.f, 0.f};
+                if (w < nw) u = *(const f32x4 *)red[w][ri];
+                const float o[4] = {u.x, u.y, u.z, u.w};
                 if (h == 0) {
 #pragma unroll
-                    for (int s = 0; s < NS; ++s) v[s] = o[s];
+                    for (int s = 0; s < 4; ++s) v[s] = o[s];
                 } else {
                     merge(v, o);
                 }
@@ -110,77 +120,84 @@ __device__ __forceinline__ void f8_reduce(float (&v)[NS], Merge merge, const Row
     }
     if constexpr (SPLIT) {
         if (a.flags & F_TEST_SKEW) {  // test only, as in device.h
-            const uint64_t ticks = (uint64_t)((c * 7 + row0 + STAGE) % 13) * 100u;
+            const uint64_t ticks = (uint64_t)((c * 7 + srow) % 13) * 100u;
             const uint64_t t0 = __builtin_amdgcn_s_memrealtime();
             while (__builtin_amdgcn_s_memrealtime() - t0 < ticks) __builtin_amdgcn_s_sleep(8);
         }
-        if (wave == 0) {
-            if (p == 0 && ri < nr && !((a.flags & F_TEST_DROP_PUBLISH) && c == 1)) {
-#pragma unroll
-                for (int x = 0; x < NX; ++x) {
-                    const float pv = v[NS - NX + x];
-                    __hip_atomic_store(slot_ptr(a, row0 + ri, STAGE, c, x),
-                                       ((unsigned long long)a.epoch << 32) | __float_as_uint(pv), __ATOMIC_RELAXED,
-                                       __HIP_MEMORY_SCOPE_AGENT);
-                }
+        if (wave == 0 && p == 0 && !((a.flags & F_TEST_DROP_PUBLISH) && c == 1)) {
+            auto publish = [&](unsigned long long *slot, float f) {
+                __hip_atomic_store(slot, ((unsigned long long)a.epoch << 32) | __float_as_uint(f), __ATOMIC_RELAXED,
+                                   __HIP_MEMORY_SCOPE_AGENT);
+            };
+            if (ri < ns) {
+                publish(slot_ptr(a, srow + ri, 0, c, 0), v[1]);
+                publish(slot_ptr(a, srow + ri, 0, c, 1), v[2]);
             }
-            constexpr int H = kMaxK / G;  // lane p of row ri polls members p, p + G, ...
-            bool ok[H][NX];
-            float g[H][NS];
-            const char *base = (const char *)slot_ptr(a, row0, STAGE, 0, 0);
-            uint32_t at[H];
-#pragma unroll
-            for (int h = 0; h < H; ++h) {
-                const int m = p + G * h;
-                const bool none = m >= a.k || ri >= nr;
-                at[h] = (uint32_t)((ri * kMaxStages * a.k + m) * a.qs * 8);
-#pragma unroll
-                for (int x = 0; x < NX; ++x) ok[h][x] = none;
-#pragma unroll
-                for (int s = 0; s < NS; ++s) g[h][s] = 0.f;
-                if constexpr (STAGE == 0) {
-                    const int64_t left = a.N - (int64_t)m * a.chunk;
-                    g[h][0] = none || left <= 0 ? 0.f : (float)(left < a.chunk ? left : a.chunk);
-                }
-            }
-            unsigned spins = 0;
-            while (true) {
-                bool all = true;
-#pragma unroll
-                for (int h = 0; h < H; ++h)
-#pragma unroll
-                    for (int x = 0; x < NX; ++x) {
-                        if (!ok[h][x]) {
-                            const unsigned long long w =
-                                __hip_atomic_load((const unsigned long long *)(base + at[h] + 8 * x), __ATOMIC_RELAXED,
-                                                  __HIP_MEMORY_SCOPE_AGENT);
-                            ok[h][x] = (unsigned)(w >> 32) == a.epoch;
-                            if (ok[h][x]) g[h][NS - NX + x] = __uint_as_float((unsigned)w);
-                        }
-                        all = all && ok[h][x];
-                    }
-                if (__all(all)) break;
-                if (++spins > a.spin_limit ||
-                    ((spins & 31u) == 0u &&
-                     __hip_atomic_load(a.errflag, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT) == a.epoch)) {
-                    if (lane == 0)
-                        __hip_atomic_store(a.errflag, a.epoch, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
-                    break;
-                }
-                __builtin_amdgcn_s_sleep(1);
-            }
-#pragma unroll
-            for (int h = 1; h < H; ++h) merge(g[0], g[h]);
-            group_levels(g[0], merge);
-            if (p == 0) {
-#pragma unroll
-                for (int s = 0; s < NS; ++s) lds.xb[ri][s] = g[0][s];
-            }
+            if (ri < na) publish(slot_ptr(a, arow + ri, 1, c, 0), v[3]);
         }
-        lds_barrier();
-#pragma unroll
-        for (int s = 0; s < NS; ++s) v[s] = lds.xb[ri][s];
     }
+}
+
+// The row group's tuples of the rows that f8_publish named.  The count of a
+// member follows from its slice.  Bounded waits as in device.h's exchange.
+__device__ __forceinline__ void f8_gather(float (&v)[4], const RowArgs &a, int64_t srow, int ns, int64_t arow, int na,
+                                          StreamF8Lds &lds) {
+    constexpr int G = kF8Group;
+    const MergeChanMax merge;
+    int lane = threadIdx.x & 63;
+    asm volatile("" : "+v"(lane));  // else what follows from it is kept in registers between calls
+    const int ri = fold_row(lane), p = lane & (G - 1);
+    if (__builtin_amdgcn_readfirstlane(threadIdx.x >> 6) == 0) {
+        constexpr int H = kMaxK / G;  // lane p of row ri polls members p, p + G, ...
+        bool ok[H][3];
+        float g[H][4];
+        // (a row's slots: stages of k members of qs words)
+        const char *sb = (const char *)slot_ptr(a, srow, 0, 0, 0), *ab = (const char *)slot_ptr(a, arow, 1, 0, 0);
+        uint32_t at[H];
+#pragma unroll
+        for (int h = 0; h < H; ++h) {
+            const int m = p + G * h;
+            const bool nos = m >= a.k || ri >= ns, noa = m >= a.k || ri >= na;
+            at[h] = (uint32_t)((ri * kMaxStages * a.k + m) * a.qs * 8);
+            ok[h][0] = ok[h][1] = nos;
+            ok[h][2] = noa;
+            const int64_t left = a.N - (int64_t)m * a.chunk;
+            g[h][0] = nos || left <= 0 ? 0.f : (float)(left < a.chunk ? left : a.chunk);
+            g[h][1] = g[h][2] = g[h][3] = 0.f;
+        }
+        unsigned spins = 0;
+        while (true) {
+            bool all = true;
+#pragma unroll
+            for (int h = 0; h < H; ++h)
+#pragma unroll
+                for (int x = 0; x < 3; ++x) {
+                    if (!ok[h][x]) {
+                        const unsigned long long w =
+                            __hip_atomic_load((const unsigned long long *)((x < 2 ? sb + 8 * x : ab) + at[h]),
+                                              __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+                        ok[h][x] = (unsigned)(w >> 32) == a.epoch;
+                        if (ok[h][x]) g[h][x + 1] = __uint_as_float((unsigned)w);
+                    }
+                    all = all && ok[h][x];
+                }
+            if (__all(all)) break;
+            if (++spins > a.spin_limit ||
+                ((spins & 31u) == 0u &&
+                 __hip_atomic_load(a.errflag, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT) == a.epoch)) {
+                if (lane == 0) __hip_atomic_store(a.errflag, a.epoch, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+                break;
+            }
+            __builtin_amdgcn_s_sleep(1);
+        }
+#pragma unroll
+        for (int h = 1; h < H; ++h) merge(g[0], g[h]);
+        group_levels(g[0], merge);
+        if (p == 0) *(f32x4 *)lds.xb[ri] = f32x4{g[0][0], g[0][1], g[0][2], g[0][3]};
+    }
+    lds_barrier();
+    const f32x4 u = *(const f32x4 *)lds.xb[ri];
+    v[0] = u.x; v[1] = u.y; v[2] = u.z; v[3] = u.w;
 }
 
 template <bool SPLIT, bool FULL>
@@ -198,14 +215,14 @@ __device__ __forceinline__ void stream_ln_fp8_rows(const RowArgs &a, int c, int 
     uint32_t off = (uint32_t)c0 + (uint32_t)tid * 16u;
     if (!FULL) off = off < rowlast ? off : rowlast;
     const bool lane_full = FULL || tid < nfv, lane_part = !FULL && tid == nfv && tn > 0;
-    const int lo = lane_part ? 16 - tn : 0;  // first own element of the partial vector
     const bool any = lane_full || lane_part;
+    const int lo = lane_part ? 16 - tn : 0;  // first own element of the partial vector
     const bool wave_full = FULL || __builtin_amdgcn_ballot_w64(lane_full) == ~0ull;
     const bool wave_part = !FULL && __builtin_amdgcn_ballot_w64(lane_part) != 0;
     const float held = FULL ? 1024.f : wave_sum(lane_full ? 16.f : lane_part ? (float)tn : 0.f);
     const float inv_held = held > 0.f ? 1.f / held : 0.f;
     const int ri = fold_row(lane);
-    const bool lead = (lane & (kF8Group - 1)) == 0;
+    const bool lead = c == 0 && tid < 64 && (lane & (kF8Group - 1)) == 0;
 
     float g[16], b[16];
     bool fin = true;
@@ -219,6 +236,12 @@ __device__ __forceinline__ void stream_ln_fp8_rows(const RowArgs &a, int c, int 
     for (int i = 0; i < 16; ++i) fin = fin && __builtin_isfinite(g[i]) && __builtin_isfinite(b[i]);
     const bool pfin = __builtin_amdgcn_ballot_w64(fin) == ~0ull;
 
+    struct Rows {
+        u32x4 x[R];
+        float xs;      // input scale of row ri
+    };
+
+    const int64_t step = (int64_t)a.groups * R;
     // The lane's row of a round, opaque: as an induction the compiler keeps a
     // 64-bit pointer per lane for each of the arrays indexed by it.
     auto here = [&]() -> uint32_t {
@@ -226,54 +249,27 @@ __device__ __forceinline__ void stream_ln_fp8_rows(const RowArgs &a, int c, int 
         asm volatile("" : "+v"(r));
         return r;
     };
-    u32x4 x[R], n[R];
-    float xs, nxs;          // input scale of row ri
-    auto issue = [&](int64_t row0, uint32_t live) {
-        uint32_t o = off & live;
+    // Loads of the rows at `row0`; past the end every lane reads the first
+    // vector of the last rows again (one line).
+    auto issue = [&](Rows &n, int64_t row0) {
+        const bool live = row0 < a.M;
+        const int64_t at = live ? row0 : a.M - 1;
+        uint32_t o = live ? off : 0u;
         asm volatile("" : "+v"(o));
 #pragma unroll
         for (int i = 0; i < R; ++i) {
-            const int64_t row = row0 + i < a.M ? row0 + i : row0;
-            n[i] = vload_nt<false>((const char *)a.in0 + row * a.ld0, o);
+            const int64_t row = at + i < a.M ? at + i : at;
+            n.x[i] = vload_nt<false>((const char *)a.in0 + row * a.ld0, o);
         }
-        const int last = a.M - row0 > R ? R - 1 : (int)(a.M - row0) - 1;
+        const int last = a.M - at > R ? R - 1 : (int)(a.M - at) - 1;
         const uint32_t rr = here();
-        nxs = (a.s0 + row0)[(int)rr < last ? rr : (uint32_t)last];
+        n.xs = (a.s0 + at)[(int)rr < last ? rr : (uint32_t)last];
     };
-    uint32_t so;
-    auto store = [&](int64_t row, bool live, u32x4 v) {
-        char *orow = (char *)a.out + row * a.ldo;
-        __amdgpu_buffer_rsrc_t rs = __builtin_amdgcn_make_buffer_rsrc(orow, 0, live ? (int)a.N : 0, 0x00020000);
-        __builtin_amdgcn_raw_buffer_store_b128(v, rs, lane_full ? so : 0x80000000u, 0, CREDIT_STORE_NT ? 2 : 0);
-        if (!FULL && live && lane_part) {
-#pragma unroll
-            for (int i = 1; i < 16; ++i)
-                if (i >= lo) (orow + so)[i] = (char)(v[i / 4] >> (8 * (i & 3)));
-        }
-    };
-
-    const int64_t step = (int64_t)a.groups * R;
-    int64_t row0 = (int64_t)grp * R;
-    if (row0 < a.M) issue(row0, 0xffffffffu);
-    __builtin_amdgcn_s_waitcnt(0);  // the loop's own waits then count its own accesses only
-    for (; row0 < a.M; row0 += step) {
-#pragma unroll
-        for (int i = 0; i < R; ++i) x[i] = n[i];
-        xs = nxs;
-        const int64_t nrow = row0 + step;
-        // (rows off their lines take longer to load: theirs go first)
-        constexpr bool EARLY = !FULL;
-        const bool poller = SPLIT && T > 64 && __builtin_amdgcn_readfirstlane(tid >> 6) == 0;
-        auto next = [&]() { issue(nrow < a.M ? nrow : row0, nrow < a.M ? 0xffffffffu : 0u); };
-        if (EARLY && !poller) next();
-        __builtin_amdgcn_sched_barrier(0);
-        const int nr = (int)(a.M - row0 < R ? a.M - row0 : R);
-        so = off;
-        asm volatile("" : "+v"(so));
-        const bool writer = c == 0 && tid < 64 && lead && ri < nr;
+    auto count = [&](int64_t row0) -> int { return (int)(row0 >= a.M ? 0 : a.M - row0 < R ? a.M - row0 : R); };
+    // (count, mean, M2) of the wave's part
+    auto moments = [&](Rows &n, float (&st)[4]) {
         // Sum and sum of squares of the codes, two elements an instruction (an
-        // e4m3 value is exact in FP16; products and sums are FP32), then (count,
-        // mean, M2) of the wave.
+        // e4m3 value is exact in FP16; products and sums are FP32).
         float s1[R], s2[R];
         if (!wave_full) {
             // codes that are not the lane's own count as 0
@@ -282,7 +278,7 @@ __device__ __forceinline__ void stream_ln_fp8_rows(const RowArgs &a, int c, int 
                 const int own = any ? 4 * w + 4 - lo : 0;  // bytes of this word, from its top
                 const unsigned m = own >= 4 ? 0xffffffffu : own <= 0 ? 0u : 0xffffffffu << (8 * (4 - own));
 #pragma unroll
-                for (int i = 0; i < R; ++i) x[i][w] &= m;
+                for (int i = 0; i < R; ++i) n.x[i][w] &= m;
             }
         }
 #pragma unroll
@@ -290,28 +286,29 @@ __device__ __forceinline__ void stream_ln_fp8_rows(const RowArgs &a, int c, int 
             s1[i] = s2[i] = 0.f;
 #pragma unroll
             for (int w = 0; w < 4; ++w) {
-                const unsigned d = x[i][w];
-#pragma unroll
-                for (int u = 0; u < 2; ++u) {
-                    const f16x2 q = __builtin_bit_cast(f16x2, u ? __builtin_amdgcn_cvt_scalef32_pk_f16_fp8(d, 1.f, true)
-                                                                : __builtin_amdgcn_cvt_scalef32_pk_f16_fp8(d, 1.f, false));
-                    s1[i] = __builtin_amdgcn_fdot2(q, f16x2{(_Float16)1.f, (_Float16)1.f}, s1[i], false);
-                    s2[i] = __builtin_amdgcn_fdot2(q, q, s2[i], false);
-                }
+                const unsigned d = n.x[i][w];
+                const f16x2 one = {(_Float16)1.f, (_Float16)1.f};
+                const f16x2 p = __builtin_bit_cast(f16x2, __builtin_amdgcn_cvt_scalef32_pk_f16_fp8(d, 1.f, false));
+                const f16x2 q = __builtin_bit_cast(f16x2, __builtin_amdgcn_cvt_scalef32_pk_f16_fp8(d, 1.f, true));
+                s1[i] = __builtin_amdgcn_fdot2(p, one, s1[i], false);
+                s2[i] = __builtin_amdgcn_fdot2(p, p, s2[i], false);
+                s1[i] = __builtin_amdgcn_fdot2(q, one, s1[i], false);
+                s2[i] = __builtin_amdgcn_fdot2(q, q, s2[i], false);
             }
             keep_order(s1[i], s2[i]);
         }
         const float mw = fold(s1, FoldSum()) * inv_held;
-        float m2 = fold(s2, FoldSum()) - held * mw * mw, mean_w = mw;
+        float m2 = fold(s2, FoldSum()) - held * mw * mw, mean = mw;
         // Where the mean is large beside the spread the difference of the two
         // has lost digits: moments about the wave's mean instead.
         if (__builtin_amdgcn_ballot_w64(!(held * mw * mw <= 2.f * m2)) != 0) {
+            opaque<R>(n.x);
 #pragma unroll
             for (int i = 0; i < R; ++i) {
                 const float m = lane_value(mw, fold_lane(i));
                 float q[16];
                 s1[i] = s2[i] = 0.f;
-                decode<DT_FP8>(x[i], q, 1.f);
+                decode<DT_FP8>(n.x[i], q, 1.f);
 #pragma unroll
                 for (int e = 0; e < 16; ++e) {
                     const float d = any && e >= lo ? q[e] - m : 0.f;
@@ -321,60 +318,66 @@ __device__ __forceinline__ void stream_ln_fp8_rows(const RowArgs &a, int c, int 
                 keep_order(s1[i], s2[i]);
             }
             const float f1 = fold(s1, FoldSum()), f2 = fold(s2, FoldSum()), r = f1 * inv_held;
-            mean_w += r;
+            mean += r;
             m2 = f2 - f1 * r;
         }
-        float st[3] = {held, held > 0.f ? mean_w : 0.f, held > 0.f ? fmaxf(m2, 0.f) : 0.f};
-        f8_reduce<SPLIT, 0, 3>(st, MergeChanSel(), a, row0, nr, c, lds, parity);
-        if (!EARLY && !poller) next();
-        const float mean = st[1], rstd = rsqrtf(xs * xs * (st[2] * invN) + a.eps);
-        const float amul = xs * rstd, bm = -mean * amul;
-        if (writer) {
+        st[0] = held;
+        st[1] = held > 0.f ? mean : 0.f;
+        st[2] = held > 0.f ? fmaxf(m2, 0.f) : 0.f;
+    };
+    // the scales by which rows are written: with the largest output `am`, 448 / am
+    struct Out {
+        float amul, bm, oinv;
+        bool plain;
+    };
+    // y = (q amul + bm) gamma + beta
+    auto finish = [&](const Rows &n, const float (&st)[4], int64_t row0, Out &o) {
+        const float mean = st[1], rstd = rsqrtf(n.xs * n.xs * (st[2] * invN) + a.eps);
+        o.amul = n.xs * rstd;
+        o.bm = -mean * o.amul;
+        if (lead && row0 + ri < a.M) {
             const uint32_t rr = here();
-            if (a.mean_out) (a.mean_out + row0)[rr] = xs * mean;
+            if (a.mean_out) (a.mean_out + row0)[rr] = n.xs * mean;
             if (a.rstd_out) (a.rstd_out + row0)[rr] = rstd;
         }
-        opaque<R>(x);
+    };
+    auto largest = [&](Rows &cur, const Out &o) -> float {
         float t[R];
+        opaque<R>(cur.x);
 #pragma unroll
         for (int i = 0; i < R; ++i) {
-            const float A = lane_value(amul, fold_lane(i)), Bm = lane_value(bm, fold_lane(i));
+            const float A = lane_value(o.amul, fold_lane(i)), Bm = lane_value(o.bm, fold_lane(i));
             float q[16], am = 0.f;
-            decode<DT_FP8>(x[i], q, 1.f);
+            decode<DT_FP8>(cur.x[i], q, 1.f);
+#pragma unroll
+            for (int e = 0; e < 16; ++e) q[e] = fmaf(fmaf(q[e], A, Bm), g[e], b[e]);
             if (wave_part) {
 #pragma unroll
-                for (int e = 0; e < 16; ++e) {
-                    const float y = fmaf(fmaf(q[e], A, Bm), g[e], b[e]);
-                    am = fmaxf(am, e >= lo ? fabsf(y) : 0.f);
-                }
+                for (int e = 0; e < 16; ++e) am = fmaxf(am, e >= lo ? fabsf(q[e]) : 0.f);
             } else {
 #pragma unroll
-                for (int e = 0; e < 16; ++e) am = fmaxf(am, fabsf(fmaf(fmaf(q[e], A, Bm), g[e], b[e])));
+                for (int e = 0; e < 16; ++e) am = fmaxf(am, fabsf(q[e]));
             }
-            if (!FULL) am = any ? am : 0.f;
-            t[i] = am;
+            t[i] = any ? am : 0.f;
             keep_order(t[i]);
         }
-        float mx[1] = {fold(t, FoldMax())};
-        f8_reduce<SPLIT, 1, 1>(mx, MergeMax1(), a, row0, nr, c, lds, parity);
-        if (poller) next();
-        const float oinv = mx[0] > 0.f ? kFp8Max / mx[0] : 1.f;
-        if (writer) (a.so + row0)[here()] = mx[0] > 0.f ? mx[0] / kFp8Max : 1.f;
-        // Finite rows scaled by 448 / amax convert without a clamp (up to 464
-        // rounds to 448); anything else takes the clamp.
-        const bool plain = pfin && __builtin_amdgcn_ballot_w64(fabsf(amul) < 1e30f && fabsf(bm) < 1e30f &&
-                                                               mx[0] < 3e38f) == ~0ull;
-        opaque<R>(x);
+        return fold(t, FoldMax());
+    };
+    auto write = [&](Rows &cur, const Out &o, int64_t row0) {
+        const int nr = count(row0);
+        uint32_t so = off;
+        asm volatile("" : "+v"(so));
+        opaque<R>(cur.x);
 #pragma unroll
         for (int i = 0; i < R; ++i) {
-            const float A = lane_value(amul, fold_lane(i)), Bm = lane_value(bm, fold_lane(i));
-            const float oi = lane_value(oinv, fold_lane(i));
+            const float A = lane_value(o.amul, fold_lane(i)), Bm = lane_value(o.bm, fold_lane(i));
+            const float oi = lane_value(o.oinv, fold_lane(i));
             float q[16];
-            decode<DT_FP8>(x[i], q, 1.f);
+            decode<DT_FP8>(cur.x[i], q, 1.f);
 #pragma unroll
             for (int e = 0; e < 16; ++e) q[e] = fmaf(fmaf(q[e], A, Bm), g[e], b[e]);
             u32x4 v;
-            if (plain) {
+            if (o.plain) {
 #pragma unroll
                 for (int w = 0; w < 4; ++w) {
                     int d = __builtin_amdgcn_cvt_pk_fp8_f32(q[4 * w] * oi, q[4 * w + 1] * oi, 0, false);
@@ -383,10 +386,100 @@ __device__ __forceinline__ void stream_ln_fp8_rows(const RowArgs &a, int c, int 
             } else {
                 v = encode<DT_FP8>(q, oi);
             }
-            store(row0 + i, i < nr, v);
+            // unconditional, dropped for lanes without a whole vector (stream.h)
+            char *orow = (char *)a.out + (row0 + i) * a.ldo;
+            __amdgpu_buffer_rsrc_t rs = __builtin_amdgcn_make_buffer_rsrc(orow, 0, i < nr ? (int)a.N : 0, 0x00020000);
+            __builtin_amdgcn_raw_buffer_store_b128(v, rs, lane_full ? so : 0x80000000u, 0, CREDIT_STORE_NT ? 2 : 0);
+            if (!FULL && i < nr && lane_part) {
+#pragma unroll
+                for (int e = 1; e < 16; ++e)
+                    if (e >= lo) (orow + so)[e] = (char)(v[e / 4] >> (8 * (e & 3)));
+            }
             __builtin_amdgcn_sched_barrier(0);
         }
+    };
+    auto scale = [&](Out &o, float am, int64_t row0) {
+        o.oinv = am > 0.f ? kFp8Max / am : 1.f;
+        if (lead && row0 + ri < a.M) (a.so + row0)[here()] = am > 0.f ? am / kFp8Max : 1.f;
+        // Finite rows scaled by 448 / amax convert without a clamp (up to 464
+        // rounds to 448); anything else takes the clamp.
+        o.plain = pfin && __builtin_amdgcn_ballot_w64(fabsf(o.amul) < 1e30f && fabsf(o.bm) < 1e30f && am < 3e38f) == ~0ull;
+    };
+
+    // A round: the largest output of the current rows and the moments of the
+    // next ones are published; the rows before, whose scale is known, are
+    // written while that is under way, the rows move up and the loads of the
+    // rows after the next are issued; then the row group's values are gathered.
+    // Wave 0, which polls, loads after that: loads return in order.
+    const bool poller = T > 64 && __builtin_amdgcn_readfirstlane(tid >> 6) == 0;
+    int64_t row0 = (int64_t)grp * R;
+    if (row0 >= a.M) return;
+    Rows prv, cur, nxt;
+    Out oc, op;  // of the current and the previous rows
+    float st[4];
+    if constexpr (!SPLIT) {
+        // Row-resident: nothing to wait for but a barrier, so two sets of rows
+        // do (4096 x 16384: 32.7 us, 37.6 with three); rows off their lines take
+        // longer to load, so theirs are issued first.
+        issue(nxt, row0);
+        __builtin_amdgcn_s_waitcnt(0);  // the loop's own waits then count its own accesses only
+        for (; row0 < a.M; row0 += step) {
+            cur = nxt;
+            if (!FULL) issue(nxt, row0 + step);
+            __builtin_amdgcn_sched_barrier(0);
+            moments(cur, st);
+            st[3] = 0.f;
+            f8_publish<SPLIT>(st, a, row0, 0, row0, 0, c, lds, parity);
+            finish(cur, st, row0, oc);
+            if (FULL) issue(nxt, row0 + step);
+            const float fm = largest(cur, oc);
+            st[0] = st[1] = st[2] = 0.f;
+            st[3] = fm;
+            f8_publish<SPLIT>(st, a, row0, 0, row0, 0, c, lds, parity);
+            scale(oc, st[3], row0);
+            write(cur, oc, row0);
+        }
+        return;
     }
+    issue(cur, row0);
+    issue(nxt, row0 + step);
+    moments(cur, st);
+    st[3] = 0.f;
+    f8_publish<SPLIT>(st, a, row0, count(row0), row0, 0, c, lds, parity);
+    f8_gather(st, a, row0, count(row0), row0, 0, lds);
+    finish(cur, st, row0, oc);
+    op = oc;
+    op.oinv = 0.f;
+    op.plain = false;
+    prv = cur;
+    __builtin_amdgcn_s_waitcnt(0);  // the loop's own waits then count its own accesses only
+    bool first = true;
+    for (; row0 < a.M; row0 += step) {
+        const int nr = count(row0), nn = count(row0 + step);
+        const float fm = largest(cur, oc);
+        moments(nxt, st);
+        st[3] = fm;
+        f8_publish<SPLIT>(st, a, row0 + step, nn, row0, nr, c, lds, parity);
+        if (!first) write(prv, op, row0 - step);
+        first = false;
+        // (made here, so that the loads go to the registers they leave)
+#pragma unroll
+        for (int i = 0; i < R; ++i) {
+            prv.x[i] = cur.x[i];
+            cur.x[i] = nxt.x[i];
+        }
+        opaque<R>(prv.x);
+        opaque<R>(cur.x);
+        cur.xs = nxt.xs;
+        keep1(cur.xs);
+        if (!poller) issue(nxt, row0 + 2 * step);
+        f8_gather(st, a, row0 + step, nn, row0, nr, lds);
+        if (poller) issue(nxt, row0 + 2 * step);
+        scale(oc, st[3], row0);
+        op = oc;
+        finish(cur, st, row0 + step, oc);
+    }
+    write(prv, op, row0 - step);
 }
 
 // FULL: every slice is one whole vector per thread (N = 16 k T).
