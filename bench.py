@@ -114,6 +114,12 @@ def kernel_symbol(C, h, op_num, dt_num, M, N, p):
     kop = op_num
     if p.variant == C.TWO_PASS:
         return f"void credit::k_twopass<{kop}, {dt_num}, {g['block']}, 4>", g["grid"] * g["block"]
+    one = C.plan_geometry(None, op_num, C.FWD if op_num < 3 else C.BWD, dt_num, M, N, p)
+    if g["block"] != one["block"] or g["vpt"] != one["vpt"]:  # the streaming form
+        if dt_num == C.FP8 and kop == 1:
+            return "void credit::k_stream_ln_fp8<", g["grid"] * g["block"]
+        name = "k_stream_softmax" if kop == 0 else "k_stream"
+        return f"void credit::{name}<{kop}, {dt_num}, {g['vpt']}, {g['rows']}, ", g["grid"] * g["block"]
     if g["rows"] > 1:  # the multi-row norm forward
         return f"void credit::k_multirow<{kop}, {dt_num}, {g['vpt']}, {g['rows']}>", g["grid"] * g["block"]
     reg = min(g["vpt"], 32)  # slices past 32 vectors per thread keep the rest in LDS
