@@ -654,7 +654,13 @@ void resolve_stream(credit_handle_t h, int k_op, int dt, int64_t M, int64_t N, L
         const int64_t all = std::min(gmax, blocks);
         int64_t busiest = 0;  // CU 0 has the first of every h->cus groups
         for (int64_t w = 0; w < all; w += h->cus) busiest += (blocks - w + all - 1) / all;
-        if (!ncp_of(k_op) && busiest < least) groups = all;
+        // A tie goes to as many as fit for FP8 softmax alone: its time is its
+        // instructions', and one workgroup of 6 to 8 waves per CU leaves half the
+        // SIMDs idle (1200 x 21535: 240 groups of 5 rounds 26.3 us, 512 groups 19.7; 2200 x
+        // 30001 44.4 against 34.5); the forms bound by memory lose (BF16 quantisation
+        // 2200 x 29001 37.9 with fewest, 43.3).
+        const bool tie = busiest == least && groups <= h->cus && f8 && k_op == OP_SOFTMAX_FWD;
+        if (!ncp_of(k_op) && (busiest < least || tie)) groups = all;
     }
     L.stream = true;
     L.chunk = cv * epv;
