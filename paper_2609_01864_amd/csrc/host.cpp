@@ -1375,15 +1375,23 @@ int bytes_rank(int c) { return c == 0 ? CREDIT_NUM_PLANS : c; }
 // training timings predate, has a better one.  Rows are then fastest with the
 // fewest members they need (BF16 LayerNorm backward 4096 x 5120: 34 us resident,
 // 46 at the network's k = 2; 4096 x 16384: 88 at k = 2 and 4, 91 at 8; forward 4096 x
-// 16384 FP32 93.8 resident, 95.8 at k = 2): the fixed rule's plan, if it streams,
-// and for the FP8 LayerNorm forward, whose one-row kernels are slower at any k,
-// the first plan that does -- the second where the first leaves one workgroup of
-// 13 to 16 waves per CU, whose barriers nothing hides (4096 x 65536 143 at k = 4, 137
-// at 8; 1500 x 100001 126 at 8, 114 at 16; 1024 x 262144 151 at 16, 146 at 32; shorter
-// rows would gain nothing: 2000 x 30000 47 at 2, 49.5 at 4).
+// 16384 FP32 93.8 resident, 95.8 at k = 2): the fixed rule's plan, if it streams.
+// Else the first plan that does, where the one-row kernels are slower at the
+// factors the network knows: LayerNorm backward up to k = 16 (FP32 898 x 32528 82 at
+// 8, 94 at the network's 4; 1000 x 50000 138 at 16, 150; 1024 x 131072 320 at 16, 327 at
+// 32), BF16 forward up to 8 (LayerNorm 2048 x 131072 196 at 8, 214 at the network's 4;
+// RMSNorm 2000 x 50000 86 at 2, 97), FP8 LayerNorm forward at any -- there the second
+// such plan where the first leaves one workgroup of 13 to 16 waves per CU, whose
+// barriers nothing hides (4096 x 65536 143 at k = 4, 137 at 8; 1500 x 100001 126 at 8,
+// 114 at 16; 1024 x 262144 151 at 16, 146 at 32; shorter rows would gain nothing: 2000 x
+// 30000 47 at 2, 49.5 at 4).
 bool stream_default(credit_handle_t h, int k_op, int dt, int64_t M, int64_t N, credit_plan_t *out) {
     if (!core_op(k_op) && !softmax_stream(k_op)) return false;
-    const bool any = k_op == OP_LN_FWD && dt == CREDIT_FP8_E4M3;
+    const bool f8 = k_op == OP_LN_FWD && dt == CREDIT_FP8_E4M3;
+    // most members of a plan that is not the fixed rule's
+    const int most = f8 ? kMaxK
+                   : k_op == OP_LN_BWD ? 16
+                   : (k_op == OP_LN_FWD || k_op == OP_RMS_FWD) && dt == CREDIT_BF16 ? 8 : 0;
     bool found = false;
     for (int c = 1; c < CREDIT_NUM_PLANS; ++c) {
         const credit_plan_t p = class_plan(c);
@@ -1391,11 +1399,10 @@ bool stream_default(credit_handle_t h, int k_op, int dt, int64_t M, int64_t N, c
         Launch L;
         if (resolve(h, k_op, dt, M, N, p, false, L) == CREDIT_OK && L.stream) {
             *out = p;
-            if (found || !any || N < 32768 || L.block <= 768) return true;
+            if (found || !f8 || N < 32768 || L.block <= 768) return true;
             found = true;
-        } else if (!any) {
-            break;  // the first legal one is the fixed rule's
         }
+        if (c + 1 < CREDIT_NUM_PLANS && class_plan(c + 1).k > most) break;  // (the first legal one is the fixed rule's)
     }
     return found;
 }
