@@ -452,7 +452,7 @@ const void *stream_fn(int k_op, int dt, int v, int r, bool split, bool full) {
 // v == 0: the one-row kernel is kept.
 struct StreamForm {
     int v = 0, r = 0, cap = 0;
-    bool many = false;  // row-resident: only for more than two rounds
+    bool many = false;  // only for more than two rounds (row-resident), five (split)
 };
 
 // LayerNorm / RMSNorm backward, back to back on MI355X (us, one-row kernel ->
@@ -496,8 +496,15 @@ StreamForm stream_form_norm_bwd(int k_op, int dt, int k, int64_t cvec) {
 // x 131072 k = 8 238 -> 198 (LayerNorm), 198 -> 181, k = 16 244 -> 221 and 195 -> 196;
 // ragged 2048 x 100001 k = 8 282 -> 200 and 242 -> 170; 4096 x 16384 k = 8 166 -> 57.
 // FP32 slices over 1024 vectors win only with few members (1024 x 131072 k = 8 190
-// -> 188, k = 16 185 against 188; ragged 1024 x 131073 k = 16 257 against 287) and BF16
-// ones over 2048 only where rows are ragged (2048 x 131072 k = 4 217 against 225).
+// -> 188, k = 16 185 against 188; ragged 1024 x 131073 k = 16 257 against 287), in
+// workgroups whose waves nearly fill a CU (LayerNorm 1400 rows of k = 4 slices of 1125
+// vectors, 5 waves, 54.0 against 63.7, 1750, 7 waves, 69.3 -> 64.5; 2100 84.4 against 90.5,
+// 3300 124 -> 117; RMSNorm 1400 51.7 against 55.4, 1750 65.8 -> 60.1; LayerNorm whole
+// slices of 1536 60.6 against 70.1) and, where slices are whole, so that the one-row
+// kernel wastes no lane, over more than five rounds (RMSNorm 300 x 65536 k = 4 31.9
+// against 35.4, 900 rows 89.3 -> 83.5); BF16 ones over 2048 only where rows are ragged
+// (2048 x 131072 k = 4 217 against 225), from 7 waves on (k = 4, 1300 rows, slices of 2500
+// vectors 111 against 114, 3300 149 -> 131).
 StreamForm stream_form_norm_fwd(int k_op, int dt, int k, int64_t cvec, bool whole, bool aligned) {
     const bool ln = k_op == OP_LN_FWD, f32 = dt == CREDIT_F32;
     if (k == 1) {
@@ -512,14 +519,18 @@ StreamForm stream_form_norm_fwd(int k_op, int dt, int k, int64_t cvec, bool whol
     if (f32) {
         if (cvec <= 512) return !whole ? StreamForm{2, 4, 0} : ln ? StreamForm{1, 4, 0} : StreamForm{2, 2, 0};
         if (cvec <= 1024) return ln ? StreamForm{2, 2, 0} : StreamForm{2, 4, 0};
-        if (cvec <= 2048 && k <= 4) return {4, 1, 0};
-        if (cvec <= 4096 && k >= 4 && k <= 8) return {8, 1, 0};
-        return {};
+        if (cvec <= 2048 && k <= 4) {
+            if (cvec <= (ln ? 1280 : 1536) || (ln && whole && cvec < 2048)) return {};
+            return {4, 1, 0, whole};
+        }
+        if (k < 4 || k > 8 || cvec > 4096 || cvec <= (ln ? 1280 : 1792)) return {};
+        if (cvec > 2048 && cvec <= (ln ? 3072 : 2816)) return {};
+        return {8, 1, 0, whole && (!ln || cvec > 2048)};
     }
     if (cvec <= 512) return {2, 2, 0};
     if (cvec <= 1024) return whole && !ln ? StreamForm{2, 4, 0} : StreamForm{2, 2, 0};
     if (cvec <= 2048) return whole ? StreamForm{4, 1, 0} : StreamForm{2, 2, 0};
-    if (cvec <= 4096 && !whole) return {8, 1, 0};
+    if (cvec > 3072 && cvec <= 4096 && !whole) return {8, 1, 0};
     return {};
 }
 
@@ -530,8 +541,11 @@ StreamForm stream_form_norm_fwd(int k_op, int dt, int k, int64_t cvec, bool whol
 // start).  Split: 2048 x 50257 k = 2 111 -> 93 and 184 -> 130, k = 4 106 -> 91 and 173
 // -> 132, FP32 forward k = 4 154 -> 145; 8192 x 3000 k = 2 55 -> 36 and 66 -> 43. Slices
 // over 512 vectors keep the one-row kernels where rows are whole lines (2048 x
-// 32768 k = 2 51.7 against 53.6 and 76 against 80), as do FP32 ones of the backward
-// (2048 x 50257 k = 8 224 against 232).
+// 32768 k = 2 51.7 against 53.6 and 76 against 80; 1431 x 71488 k = 2 89 against 106), as do
+// FP32 ones of the backward (2048 x 50257 k = 8 224 against 232) and slices of 9 waves
+// (900 rows of 4400 vectors k = 2 70.2 against 74.1; 6100 88.3 -> 82.4).  Resident BF16 rows
+// of one workgroup per CU take more than two rounds (400 x 64800 23.1 against 25.2, 900
+// rows 53.3 -> 49.8).
 //
 // FP8 (forward): 4 vectors a lane, their exponentials kept, so that each is taken
 // once, where slices are whole vectors of every lane (4096 x 65536 113 -> 95, 1024 x
@@ -540,7 +554,7 @@ StreamForm stream_form_norm_fwd(int k_op, int dt, int k, int64_t cvec, bool whol
 // 16400 20.4 against 22.6, 1500 x 100001 k = 4 96.4 against 99.9), nor do 9 to 12 waves,
 // one workgroup per CU (3000 x 33333 67.9 against 69.6).
 StreamForm stream_form_softmax(int k_op, int dt, int k, int64_t cvec, int64_t N) {
-    const bool fwd = k_op == OP_SOFTMAX_FWD, lines = N % (16 * dt_epv(dt)) == 0;
+    const bool fwd = k_op == OP_SOFTMAX_FWD, lines = N % (8 * dt_epv(dt)) == 0;
     if (dt == CREDIT_FP8_E4M3) {
         const bool whole = N == k * cvec * 16 && cvec % 256 == 0;
         return cvec <= 4096 && (whole || (k == 1 && N % 16 && cvec + 9 <= 4096 && (cvec + 9 <= 2048 || cvec > 3072))) ? StreamForm{4, 1, 0} : StreamForm{};
@@ -550,7 +564,8 @@ StreamForm stream_form_softmax(int k_op, int dt, int k, int64_t cvec, int64_t N)
     if (k > 1 && (lines || (dt == CREDIT_F32 && !fwd))) return {};
     // up to 8 vectors more than the slice's (stream_softmax.h)
     if (cvec + 9 <= 4096) return {4, 1, 0};
-    if (fwd && cvec + 9 <= 8192) return {8, 1, 0};
+    if (k > 1 && cvec + 9 <= 4608) return {};
+    if (fwd && cvec + 9 <= 8192) return {8, 1, 0, k == 1 && dt != CREDIT_F32 && cvec + 9 > 6144};
     return {};
 }
 
@@ -623,7 +638,7 @@ void resolve_stream(credit_handle_t h, int k_op, int dt, int64_t M, int64_t N, L
     const int64_t blocks = (M + f.r - 1) / f.r;
     if (gmax < 1) return;
     const bool bwd = k_op == OP_LN_BWD || k_op == OP_RMS_BWD;
-    if (L.k > 1 ? blocks < gmax || (!bwd && blocks <= (f8 ? 3 : 2) * gmax)
+    if (L.k > 1 ? blocks < gmax || (!bwd && blocks <= (f.many ? 5 : f8 ? 3 : 2) * gmax)
                 : blocks < std::min<int64_t>(gmax, h->cus) || (f.many && blocks <= 2 * gmax))
         return;
     int64_t groups = 0;
