@@ -227,20 +227,25 @@ __device__ __forceinline__ void stream_softmax_rows(const RowArgs &a, int c, int
                 float q[EPV], g[EPV];
                 decode<DT>(x0[i][j], q, 1.f);
                 if constexpr (BW) decode<DT>(x1[i][j], g, 1.f);
+                float x[EPV];
+#pragma unroll
+                for (int e = 0; e < EPV; ++e) x[e] = fast_exp2(fmaf(q[e], FP8 ? K : kLog2e, cs));
                 if constexpr (FP8 && !FULL) {
+                    // the exponential is masked, not the code: the row's factor
+                    // may be 0 (a row of zeros quantised by its largest value),
+                    // and -inf times it NaN
                     if (__builtin_amdgcn_ballot_w64(whole(j, ph[i])) != ~0ull) {
                         int lo, hi;
                         bounds(j, ph[i], lo, hi);
 #pragma unroll
-                        for (int e = 0; e < EPV; ++e) q[e] = e >= lo && e < hi ? q[e] : -INFINITY;
+                        for (int e = 0; e < EPV; ++e) x[e] = e >= lo && e < hi ? x[e] : 0.f;
                     }
                 }
 #pragma unroll
                 for (int e = 0; e < EPV; ++e) {
-                    const float x = fast_exp2(fmaf(q[e], FP8 ? K : kLog2e, cs));
-                    s += x;
-                    if constexpr (BW) t = fmaf(x, g[e], t);
-                    if constexpr (KEEP) ev[i][j * EPV + e] = x;
+                    s += x[e];
+                    if constexpr (BW) t = fmaf(x[e], g[e], t);
+                    if constexpr (KEEP) ev[i][j * EPV + e] = x[e];
                 }
                 keep_order(s, t);
             }
