@@ -617,13 +617,14 @@ void resolve_stream(credit_handle_t h, int k_op, int dt, int64_t M, int64_t N, L
     else if (k_op == OP_QUANT_I8) f = stream_form_quant(dt, L.k, cvec);
     else if (softmax_stream(k_op)) f = stream_form_softmax(k_op, dt, L.k, cvec, N);
     if (!f.v) return;
-    // vectors of a slice: the softmax family's rows begin up to 126 bytes into
-    // their first line (stream_softmax.h), and its slices are whole lines
+    // vectors of a slice: the softmax family's rows begin up to an element short
+    // of 128 bytes into their first line (stream_softmax.h), and its slices are
+    // whole lines
     int w = (int)((cvec + 64 * f.v - 1) / (64 * f.v));
     const bool full = N == (int64_t)L.k * f.v * w * 64 * epv;
     int64_t cv = cvec;
     if (!full && stream_phase(k_op, f.v)) {
-        cv = ((N * dt_bytes(dt) + 126 + 15) / 16 + L.k - 1) / L.k;
+        cv = ((N * dt_bytes(dt) + 128 - dt_bytes(dt) + 15) / 16 + L.k - 1) / L.k;
         if (L.k > 1) cv = (cv + 7) / 8 * 8;
         w = (int)((cv + 64 * f.v - 1) / (64 * f.v));
     }
