@@ -527,7 +527,10 @@ __device__ __forceinline__ void stream_rows(const RowArgs &a, int c, int grp, St
                     const float m = s1 * inv_held;
                     st[i][0] = held;
                     st[i][1] = held > 0.f ? (ms - kf[i]) + m : 0.f;
-                    st[i][2] = held > 0.f ? fmaxf(s2 - s1 * m, 0.f) : 0.f;
+                    // held at 0 from below, but not where it is NaN (a row with a
+                    // NaN or an infinity): fmaxf would make that 0
+                    const float m2 = s2 - s1 * m;
+                    st[i][2] = held > 0.f && !(m2 < 0.f) ? m2 : 0.f;
                 }
             }
             stream_reduce<OP, R, SPLIT>(st, a, row0, nr, c, lds, parity);

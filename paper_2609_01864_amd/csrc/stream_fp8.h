@@ -323,7 +323,7 @@ __device__ __forceinline__ void stream_ln_fp8_rows(const RowArgs &a, int c, int 
         }
         st[0] = held;
         st[1] = held > 0.f ? mean : 0.f;
-        st[2] = held > 0.f ? fmaxf(m2, 0.f) : 0.f;
+        st[2] = held > 0.f && !(m2 < 0.f) ? m2 : 0.f;  // NaN stays (stream.h)
     };
     // the scales by which rows are written: with the largest output `am`, 448 / am
     struct Out {

@@ -1,6 +1,6 @@
 """Rows with special values in the streaming forms, each against the FP64 result or
-the one-row kernels' of the same row: row scales of 0, and rows whose first byte
-is the last of a line.  A cap on the row groups
+the one-row kernels' of the same row: row scales of 0, rows whose first byte
+is the last of a line, NaN and infinities under LayerNorm.  A cap on the row groups
 makes a few rows enough for a plan to stream."""
 import pytest
 import torch
@@ -54,4 +54,48 @@ def test_fp8_softmax_of_rows_at_the_end_of_a_line(capped, waves):
     v = ref / ys.double()[:, None]
     step = torch.clamp(2.0 ** torch.floor(torch.log2(v.clamp_min(2.0 ** -6))) / 8, min=2.0 ** -9)
     assert bool(((y.double() - v).abs() <= step + 1e-5 * v).all())
+    assert capped.check_errors() == C.OK
+
+
+TD = {"f32": torch.float32, "bf16": torch.bfloat16}
+
+
+# rows held by one wave, by several, and by the members of a split row
+@pytest.mark.parametrize("N,k", [(8, 1), (130, 1), (512, 1), (1000, 1), (1024, 1), (5003, 1), (512, 4), (5003, 4)])
+@pytest.mark.parametrize("dtype", ["f32", "bf16", "fp8"])
+def test_layernorm_of_rows_with_nan_or_infinity(capped, dtype, N, k):
+    M = 33
+    p = C.plan("split", k) if k > 1 else C.plan("resident")
+    if dtype == "fp8" and N < 16:
+        N = 16
+    print(f"[special] layernorm nan / inf {dtype} {M} x {N} {p}", flush=True)
+    x = torch.randn((M, N), device="cuda") + 10
+    bad = {1: (N // 2 + 3, float("nan")), 6: (0, float("nan")), 11: (N - 1, float("nan"))}
+    if dtype != "fp8":  # e4m3 has no infinity
+        bad |= {14: (N // 2 + 3, float("inf")), 17: (0, float("inf")), 20: (N - 1, -float("inf"))}
+    g, b = torch.rand(N, device="cuda") + 0.5, torch.randn(N, device="cuda")
+    if dtype == "fp8":
+        q = x.to(torch.float8_e4m3fn)
+        w = q.clone()
+        for r, (c, _) in bad.items():
+            w.view(torch.uint8)[r, c] = 0x7F
+        s = torch.rand(M, device="cuda") + 0.5
+    else:
+        q, s = x.to(TD[dtype]), None
+        w = q.clone()
+        for r, (c, v) in bad.items():
+            w[r, c] = v
+        w[23] = float("inf")
+        bad[23] = (0, float("inf"))
+    good = C.layernorm_fwd(q, g, b, x_scale=s, p=p, h=capped)
+    y, ys, mean, rstd = C.layernorm_fwd(w, g, b, x_scale=s, p=p, h=capped)
+    rows = sorted(bad)
+    # the variance of a row with a NaN or an infinity is NaN, in FP64 too
+    assert bool(torch.isnan(rstd[rows]).all()) and not bool(torch.isfinite(mean[rows]).any())
+    if dtype != "fp8":
+        assert bool(torch.isnan(y[rows].float()).all())
+    keep = [r for r in range(M) if r not in bad]
+    for a, e in zip((y, ys, mean, rstd), good):
+        if a is not None:
+            assert torch.equal(a[keep].view(torch.uint8), e[keep].view(torch.uint8))
     assert capped.check_errors() == C.OK
