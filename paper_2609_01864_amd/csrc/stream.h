@@ -357,6 +357,13 @@ __device__ __forceinline__ void stream_rows(const RowArgs &a, int c, int grp, St
         }
     }
     const float inv_held = held > 0.f ? 1.f / held : 0.f;
+    // lanes that hold an element of slot 0, as a reciprocal of their number
+    const bool lane0 = FULL || jp > 0 || lane_full || lane_part;
+    float inv_l0 = 0x1p-6f;
+    if constexpr (OP == OP_LN_FWD && !FULL) {
+        const int n = __builtin_popcountll(__builtin_amdgcn_ballot_w64(lane0));
+        inv_l0 = n ? 1.f / (float)n : 0.f;
+    }
 
     u32x4 x0[R][V], x1[TWO ? R : 1][TWO ? V : 1];
     u32x4 n0[R][V], n1[TWO ? R : 1][TWO ? V : 1];
@@ -494,12 +501,17 @@ __device__ __forceinline__ void stream_rows(const RowArgs &a, int c, int grp, St
                     }
                     st[i][0] = wave_sum(s);
                 } else {
-                    // moments about the mean of the lanes' first elements (any
-                    // element of the row serves), then (count, mean about the
-                    // row's first element, M2) of the wave
+                    // moments about the mean of one own element per lane, then
+                    // (count, mean about the row's first element, M2) of the
+                    // wave.  A lane past the slice has no vote: all of them hold
+                    // the row's last vector, and a large first element of it
+                    // would draw the shift away from the mean (rows of 132
+                    // elements with one 100 spreads out: error of rstd up to 300
+                    // roundings, 3 without)
                     float q[EPV];
                     decode<DT>(x0[i][0], q, 1.f);
-                    const float ms = wave_sum(q[0] * 0x1p-6f);
+                    const float q0 = !FULL && jp == 0 && lane_part ? q[EPV - 1] : q[0];
+                    const float ms = wave_sum(lane0 ? q0 * inv_l0 : 0.f);
                     float s1 = 0.f, s2 = 0.f;
 #pragma unroll
                     for (int j = 0; j < V; ++j) {

@@ -1,6 +1,6 @@
 """Rows with special values in the streaming forms, each against the FP64 result or
 the one-row kernels' of the same row: row scales of 0, rows whose first byte
-is the last of a line, NaN and infinities under LayerNorm.  A cap on the row groups
+is the last of a line, NaN, infinities and lone large elements under LayerNorm.  A cap on the row groups
 makes a few rows enough for a plan to stream."""
 import pytest
 import torch
@@ -98,4 +98,25 @@ def test_layernorm_of_rows_with_nan_or_infinity(capped, dtype, N, k):
     for a, e in zip((y, ys, mean, rstd), good):
         if a is not None:
             assert torch.equal(a[keep].view(torch.uint8), e[keep].view(torch.uint8))
+    assert capped.check_errors() == C.OK
+
+
+# slices of one wave whose lanes are mostly idle, and of a second wave with few
+@pytest.mark.parametrize("dtype,N", [("f32", 67), ("f32", 132), ("bf16", 132), ("bf16", 260), ("f32", 530), ("bf16", 1050)])
+def test_layernorm_of_rows_with_one_large_element(capped, dtype, N):
+    M, epv = 66, 4 if dtype == "f32" else 8
+    print(f"[special] layernorm spike {dtype} {M} x {N}", flush=True)
+    gen = torch.Generator(device="cuda").manual_seed(N)
+    x = torch.randn((M, N), device="cuda", generator=gen)
+    x[:, N - epv] = 40 + 60 * torch.rand(M, device="cuda", generator=gen)
+    x = x.to(TD[dtype])
+    g, b = torch.ones(N, device="cuda"), torch.zeros(N, device="cuda")
+    _, _, mean, rstd = C.layernorm_fwd(x, g, b, p=C.plan("resident"), h=capped)
+    xd = x.double()
+    rs = 1 / torch.sqrt(xd.var(1, correction=0) + 1e-5)
+    # M2 = sum d^2 - (sum d)^2 / n about a shift of at most a twelfth of the
+    # element: the sum of squares is at most 1.4 M2, of 16 terms a lane and 8
+    # more roundings; half of their relative error in rstd, and 4 of its own
+    assert bool(((rstd.double() / rs - 1).abs() <= (0.5 * 1.4 * 24 + 4) * 2.0 ** -24).all())
+    assert bool(((mean.double() - xd.mean(1)).abs() <= 8 * 2.0 ** -24 * xd.abs().amax(1)).all())
     assert capped.check_errors() == C.OK
