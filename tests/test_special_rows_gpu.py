@@ -1,6 +1,7 @@
 """Rows with special values in the streaming forms, each against the FP64 result or
 the one-row kernels' of the same row: row scales of 0, rows whose first byte
-is the last of a line, NaN, infinities and lone large elements under LayerNorm.  A cap on the row groups
+is the last of a line, NaN, infinities and lone large elements under LayerNorm,
+constant FP8 rows.  A cap on the row groups
 makes a few rows enough for a plan to stream."""
 import pytest
 import torch
@@ -119,4 +120,31 @@ def test_layernorm_of_rows_with_one_large_element(capped, dtype, N):
     # more roundings; half of their relative error in rstd, and 4 of its own
     assert bool(((rstd.double() / rs - 1).abs() <= (0.5 * 1.4 * 24 + 4) * 2.0 ** -24).all())
     assert bool(((mean.double() - xd.mean(1)).abs() <= 8 * 2.0 ** -24 * xd.abs().amax(1)).all())
+    assert capped.check_errors() == C.OK
+
+
+@pytest.mark.parametrize("N,k", [(16, 1), (1000, 1), (1024, 1), (5001, 1), (16384, 1), (4096, 4), (20001, 8)])
+def test_fp8_layernorm_of_constant_rows(capped, N, k):
+    # x - mean is 0 in every element, so y is beta, whatever 1 / sqrt(eps) times the value
+    M = 17
+    p = C.plan("split", k) if k > 1 else C.plan("resident")
+    print(f"[special] fp8 layernorm constant {M} x {N} {p}", flush=True)
+    q = (torch.randn((M, N), device="cuda") * 50).clamp(-448, 448).to(torch.float8_e4m3fn)
+    for r, v in ((2, 448.0), (5, -416.0), (6, 1.125), (11, 0.0), (16, 104.0)):
+        q[r] = v
+    rows = [2, 5, 6, 11, 16]
+    s = torch.rand(M, device="cuda") + 0.5
+    g, b = torch.rand(N, device="cuda") + 0.5, torch.randn(N, device="cuda")
+    one = C.Handle(0)
+    try:
+        for beta in (torch.zeros(N, device="cuda"), b):
+            y, ys, mean, rstd = C.layernorm_fwd(q, g, beta, x_scale=s, p=p, h=capped)
+            w, ws, _, _ = C.layernorm_fwd(q, g, beta, x_scale=s, p=p, h=one)
+            amax = beta.abs().max()
+            want = (amax / 448 if amax > 0 else torch.ones_like(amax)).expand(len(rows))
+            assert torch.allclose(ys[rows], want, rtol=2.0 ** -23, atol=0)
+            assert torch.equal(ys[rows], ws[rows]) and torch.equal(y.view(torch.uint8)[rows], w.view(torch.uint8)[rows])
+            assert torch.equal(mean[rows], (q[rows, 0].float() * s[rows]))
+    finally:
+        one.close()
     assert capped.check_errors() == C.OK
