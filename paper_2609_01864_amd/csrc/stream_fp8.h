@@ -420,8 +420,10 @@ __device__ __forceinline__ void stream_ln_fp8_rows(const RowArgs &a, int c, int 
         o.oinv = am > 0.f ? kFp8Max / am : 1.f;
         if (lead && row0 + ri < a.M) (a.so + row0)[here()] = am > 0.f ? am / kFp8Max : 1.f;
         // Finite rows scaled by 448 / amax convert without a clamp (up to 464
-        // rounds to 448); anything else takes the clamp.
-        o.plain = pfin && __builtin_amdgcn_ballot_w64(fabsf(o.amul) < 1e30f && fabsf(o.bm) < 1e30f && am < 3e38f) == ~0ull;
+        // rounds to 448); anything else takes the clamp, so do rows so small that
+        // 448 / amax is infinite.
+        o.plain = pfin && __builtin_amdgcn_ballot_w64(fabsf(o.amul) < 1e30f && fabsf(o.bm) < 1e30f && am < 3e38f &&
+                                                      o.oinv < 3e38f) == ~0ull;
     };
 
     // A round: the largest output of the current rows and the moments of the

@@ -1,7 +1,7 @@
 """Rows with special values in the streaming forms, each against the FP64 result or
 the one-row kernels' of the same row: row scales of 0, rows whose first byte
 is the last of a line, NaN, infinities and lone large elements under LayerNorm,
-constant FP8 rows.  A cap on the row groups
+constant FP8 rows and FP8 rows of tiny outputs.  A cap on the row groups
 makes a few rows enough for a plan to stream."""
 import pytest
 import torch
@@ -126,7 +126,7 @@ def test_layernorm_of_rows_with_one_large_element(capped, dtype, N):
 @pytest.mark.parametrize("N,k", [(16, 1), (1000, 1), (1024, 1), (5001, 1), (16384, 1), (4096, 4), (20001, 8)])
 def test_fp8_layernorm_of_constant_rows(capped, N, k):
     # x - mean is 0 in every element, so y is beta, whatever 1 / sqrt(eps) times the value
-    M = 17
+    M = 29  # over three rounds of two groups of four rows
     p = C.plan("split", k) if k > 1 else C.plan("resident")
     print(f"[special] fp8 layernorm constant {M} x {N} {p}", flush=True)
     q = (torch.randn((M, N), device="cuda") * 50).clamp(-448, 448).to(torch.float8_e4m3fn)
@@ -145,6 +145,29 @@ def test_fp8_layernorm_of_constant_rows(capped, N, k):
             assert torch.allclose(ys[rows], want, rtol=2.0 ** -23, atol=0)
             assert torch.equal(ys[rows], ws[rows]) and torch.equal(y.view(torch.uint8)[rows], w.view(torch.uint8)[rows])
             assert torch.equal(mean[rows], (q[rows, 0].float() * s[rows]))
+    finally:
+        one.close()
+    assert capped.check_errors() == C.OK
+
+
+@pytest.mark.parametrize("N,k", [(512, 1), (5001, 1), (4096, 4)])
+def test_fp8_layernorm_of_tiny_outputs(capped, N, k):
+    # 448 / amax is infinite below 1.3e-36: the codes saturate
+    M = 29  # over three rounds of two groups of four rows
+    p = C.plan("split", k) if k > 1 else C.plan("resident")
+    print(f"[special] fp8 layernorm tiny outputs {M} x {N} {p}", flush=True)
+    q = (torch.randn((M, N), device="cuda") * 50).clamp(-448, 448).to(torch.float8_e4m3fn)
+    s = torch.rand(M, device="cuda") + 0.5
+    b = torch.zeros(N, device="cuda")
+    one = C.Handle(0)
+    try:
+        for scale in (1e-30, 1e-36, 1e-37):
+            g = (torch.rand(N, device="cuda") + 0.5) * scale
+            y, ys, _, _ = C.layernorm_fwd(q, g, b, x_scale=s, p=p, h=capped)
+            w, _, _, _ = C.layernorm_fwd(q, g, b, x_scale=s, p=p, h=one)
+            assert not bool(torch.isnan(y.float()).any())
+            if scale == 1e-37:  # every code is +-448
+                assert torch.equal(y.view(torch.uint8), w.view(torch.uint8))
     finally:
         one.close()
     assert capped.check_errors() == C.OK
