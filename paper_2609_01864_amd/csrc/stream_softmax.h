@@ -250,7 +250,24 @@ __device__ __forceinline__ void stream_softmax_rows(const RowArgs &a, int c, int
                 keep_order(s, t);
             }
             st[i][1] = wave_sum(s) * USH;
-            if constexpr (BW) st[i][S::NS - 1] = wave_sum(t) * USH;
+            if constexpr (BW) {
+                t = wave_sum(t);
+                if (SH != 0.f && __builtin_expect(!(fabsf(t) < INFINITY), 0)) {
+                    // gradients from 2^96 on: the terms without their 2^32
+                    t = 0.f;
+#pragma unroll
+                    for (int j = 0; j < V; ++j) {
+                        if (empty(j, ph[i])) continue;
+                        float g[EPV];
+                        decode<DT>(x1[i][j], g, 1.f);
+#pragma unroll
+                        for (int e = 0; e < EPV; ++e) t = fmaf(ev[KEEP ? i : 0][KEEP ? j * EPV + e : 0] * USH, g[e], t);
+                    }
+                    st[i][S::NS - 1] = wave_sum(t);
+                } else {
+                    st[i][S::NS - 1] = t * USH;
+                }
+            }
         }
         stream_reduce<OP, R, SPLIT>(st, a, row0, nr, c, lds, parity);
         if constexpr (!KEEP) fresh();

@@ -1,7 +1,7 @@
 """Rows with special values in the streaming forms, each against the FP64 result or
 the one-row kernels' of the same row: row scales of 0, rows whose first byte
 is the last of a line, NaN, infinities and lone large elements under LayerNorm,
-constant FP8 rows and FP8 rows of tiny outputs.  A cap on the row groups
+constant FP8 rows, FP8 rows of tiny outputs and huge gradients.  A cap on the row groups
 makes a few rows enough for a plan to stream."""
 import pytest
 import torch
@@ -170,4 +170,23 @@ def test_fp8_layernorm_of_tiny_outputs(capped, N, k):
                 assert torch.equal(y.view(torch.uint8), w.view(torch.uint8))
     finally:
         one.close()
+    assert capped.check_errors() == C.OK
+
+
+# slices held one, two and four vectors a lane
+@pytest.mark.parametrize("N,k", [(200, 1), (2000, 1), (4111, 1), (9001, 1), (30001, 4)])
+@pytest.mark.parametrize("dtype", ["f32", "bf16"])
+def test_logits_backward_of_huge_gradients(capped, dtype, N, k):
+    # the gradient is linear, and a power of two is exact at every step of it
+    M = 17
+    p = C.plan("split", k) if k > 1 else C.plan("resident")
+    print(f"[special] logits backward, huge gradients {dtype} {M} x {N} {p}", flush=True)
+    x = (3 * torch.randn((M, N), device="cuda")).to(TD[dtype])
+    dy = torch.randn((M, N), device="cuda").to(TD[dtype])
+    dx, _ = C.softmax_logits_bwd(x, dy, p=p, h=capped)
+    for e in (40, 100, 112):
+        got, _ = C.softmax_logits_bwd(x, dy * 2.0 ** e, p=p, h=capped)
+        assert bool(torch.isfinite(got.float()).all())
+        big = dx.float().abs() > 2.0 ** -100
+        assert torch.equal(got.double()[big], dx.double()[big] * 2.0 ** e)
     assert capped.check_errors() == C.OK
