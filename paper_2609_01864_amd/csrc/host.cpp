@@ -1402,7 +1402,6 @@ int bytes_rank(int c) { return c == 0 ? CREDIT_NUM_PLANS : c; }
 // 114 at 16; 1024 x 262144 151 at 16, 146 at 32; shorter rows would gain nothing: 2000 x
 // 30000 47 at 2, 49.5 at 4).
 bool stream_default(credit_handle_t h, int k_op, int dt, int64_t M, int64_t N, credit_plan_t *out) {
-    if (!core_op(k_op) && !softmax_stream(k_op)) return false;
     const bool f8 = k_op == OP_LN_FWD && dt == CREDIT_FP8_E4M3;
     // most members of a plan that is not the fixed rule's
     const int most = f8 ? kMaxK

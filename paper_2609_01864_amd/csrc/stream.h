@@ -399,12 +399,12 @@ __device__ __forceinline__ void stream_rows(const RowArgs &a, int c, int grp, St
             }
         }
     };
-    // masks of a slot's packed data: `fill` in the elements that are not its own
-    auto mask = [&](u32x4 &d, int j, unsigned fill) {
+    // elements of a slot that are not the lane's own become 0
+    auto mask = [&](u32x4 &d, int j) {
         if constexpr (!FULL) {
             if (j < jp) return;
             if (j > jp) {
-                d = u32x4{fill, fill, fill, fill};
+                d = u32x4{0u, 0u, 0u, 0u};
                 return;
             }
 #pragma unroll
@@ -412,7 +412,7 @@ __device__ __forceinline__ void stream_rows(const RowArgs &a, int c, int grp, St
                 unsigned m = 0u;
                 if constexpr (B == 4) m = own(w) ? 0xffffffffu : 0u;
                 else m = (own(2 * w) ? 0xffffu : 0u) | (own(2 * w + 1) ? 0xffff0000u : 0u);
-                d[w] = (d[w] & m) | (fill & ~m);
+                d[w] &= m;
             }
         }
     };
@@ -492,7 +492,7 @@ __device__ __forceinline__ void stream_rows(const RowArgs &a, int c, int grp, St
                     float s = 0.f;
 #pragma unroll
                     for (int j = 0; j < V; ++j) {
-                        mask(x0[i][j], j, 0u);
+                        mask(x0[i][j], j);
                         float q[EPV];
                         decode<DT>(x0[i][j], q, 1.f);
 #pragma unroll
@@ -546,8 +546,6 @@ __device__ __forceinline__ void stream_rows(const RowArgs &a, int c, int grp, St
                 }
             }
             stream_reduce<OP, R, SPLIT>(st, a, row0, nr, c, lds, parity);
-            if constexpr (LATE)
-                if (poller) next();
             fresh();
 #pragma unroll
             for (int i = 0; i < R; ++i) {
@@ -584,8 +582,8 @@ __device__ __forceinline__ void stream_rows(const RowArgs &a, int c, int grp, St
 #pragma unroll
                 for (int j = 0; j < V; ++j) {
                     if (!FULL && j > jp) continue;
-                    mask(x0[i][j], j, 0u);
-                    mask(x1[i][j], j, 0u);
+                    mask(x0[i][j], j);
+                    mask(x1[i][j], j);
                     if (i > 0)
 #pragma unroll
                         for (int w = 0; w < 4; ++w) x1[i][j][w] = live ? x1[i][j][w] : 0u;
