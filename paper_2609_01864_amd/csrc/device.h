@@ -35,6 +35,37 @@ __device__ __forceinline__ float fast_exp2(float v) { return __builtin_amdgcn_ex
 // under 1.2e-38 (FP32) or far below an e4m3 step (FP8).
 constexpr float kExpShift = 32.f;
 constexpr float kExpUnshift = 0x1p-32f;
+// Base-2 references c = max q log2(e) from 2^29 on are "far".  A float spacing is 64
+// or more there: 32 - c loses the shift above, and what q log2(e) - c rounds to is
+// as large as an exponent, so a row masked throughout with -1e9 (uniform) came out
+// as zeros and one masked with -1e10 or the type's lowest value as NaN.  A thread (in
+// the streaming kernels a wave) whose c is far subtracts its maximum m from q
+// before the multiplication and takes c as 0 in the exponent; c itself, held
+// finite, only ranks it among the others.  (Two whose maxima are neighbouring FP32
+// numbers may have the same c, and then count alike.)  FP8 codes do not reach it.
+// One-row BF16 rows kept in LDS pay 5% for the subtraction (1024 x 131072 139 ->
+// 146 us), two-pass ones 2.5%, the others 0 to 2%; a branch around it saves the
+// register slots nothing and costs them occupancy.
+constexpr float kFar = 0x1p29f, kFltMax = 0x1.fffffep+127f;
+__device__ __forceinline__ bool far_ref(float c) { return fabsf(c) >= kFar; }
+__device__ __forceinline__ float base2_ref(float qmax, float K) {
+    return qmax == -INFINITY ? -INFINITY : __builtin_amdgcn_fmed3f(qmax * K, -kFltMax, kFltMax);
+}
+// Exponents of a thread's logits about its reference: (q - m) K + about() in its sums,
+// (q - m) K + out(shift, c of the row) in its output.
+template <bool FP8> struct FarRef {
+    float ct, m;
+    __device__ __forceinline__ FarRef(float c, float qmax) {
+        ct = c == -INFINITY ? 0.f : c;
+        m = far() ? qmax : 0.f;
+    }
+    __device__ __forceinline__ bool far() const { return !FP8 && far_ref(ct); }
+    __device__ __forceinline__ float less(float q) const { return FP8 ? q : q - m; }
+    __device__ __forceinline__ float about() const { return far() ? 0.f : -ct; }
+    __device__ __forceinline__ float out(float shift, float cmax) const {
+        return far() ? shift + (ct - cmax) : shift - cmax;
+    }
+};
 
 // ------------------------------------------------------------------ codecs
 // Decode one 16-byte vector into EPV floats; FP8 codes are multiplied by the

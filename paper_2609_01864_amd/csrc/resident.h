@@ -432,10 +432,9 @@ __device__ __forceinline__ void row_loop(const RowArgs &a, int c, int grp, const
                 decode<DT>(t0, q, 1.f);
                 for (int i = 0; i < tn; ++i) qmax = fmaxf(qmax, q[i]);
             }
-            // held finite for a thread whose elements are all the type's lowest
-            // value (a mask): its exponentials would be inf, and inf * 0 NaN
-            float st[2] = {qmax == -INFINITY ? -INFINITY : fmaxf(qmax * K, -0x1.fffffep+127f), 0.f};
-            const float ct = qmax == -INFINITY ? 0.f : st[0];
+            float st[2] = {base2_ref(qmax, K), 0.f};
+            const FarRef<FP8> ref(st[0], qmax);
+            const float nct = ref.about();
             fresh();
 #pragma unroll
             for (int j = 0; j < VPT; ++j) {
@@ -444,7 +443,7 @@ __device__ __forceinline__ void row_loop(const RowArgs &a, int c, int grp, const
                 const bool ok = ok_of(j);
 #pragma unroll
                 for (int i = 0; i < EPV; ++i) {
-                    ev[i] = fast_exp2(fmaf(EC ? ec[j * EPV + i] : q[i], K, -ct));
+                    ev[i] = fast_exp2(fmaf(ref.less(EC ? ec[j * EPV + i] : q[i]), K, nct));
                     if constexpr (EC) ec[j * EPV + i] = ev[i];
                     st[1] += ok ? ev[i] : 0.f;
                 }
@@ -459,13 +458,13 @@ __device__ __forceinline__ void row_loop(const RowArgs &a, int c, int grp, const
                 decode<DT>(LD(l), q, 1.f);
                 const bool ok = ok_of(VPT + l);
 #pragma unroll
-                for (int i = 0; i < EPV; ++i) st[1] += ok ? fast_exp2(fmaf(q[i], K, -ct)) : 0.f;
+                for (int i = 0; i < EPV; ++i) st[1] += ok ? fast_exp2(fmaf(ref.less(q[i]), K, nct)) : 0.f;
                 keep_order(st[1]);
             }
             if (tail) {
                 float q[EPV];
                 decode<DT>(t0, q, 1.f);
-                for (int i = 0; i < tn; ++i) st[1] += fast_exp2(fmaf(q[i], K, -ct));
+                for (int i = 0; i < tn; ++i) st[1] += fast_exp2(fmaf(ref.less(q[i]), K, nct));
             }
             row_reduce<2>(st, MergeSoftmax(), a, row, 0, c, red, xb, parity);
             const float cmax = st[0];
@@ -473,15 +472,15 @@ __device__ __forceinline__ void row_loop(const RowArgs &a, int c, int grp, const
             // FP8 output: the largest output is 2^0 * inv_s, so amax = inv_s and the
             // code of element i is 448 * 2^(q*K - c) (no second statistics stage).
             const float omul = FP8 ? kFp8Max : inv_s;
-            const float csh = kExpShift - cmax, omuls = omul * kExpUnshift;
+            const float csh = ref.out(kExpShift, cmax), omuls = omul * kExpUnshift;
             if (FP8 && writer) a.so[row] = inv_s / kFp8Max;
             if constexpr (EC || ECI) {
-                // ct <= cmax, so the exponent is at most 32 for a thread with a
+                // The thread's reference is at most cmax, so the exponent is at most 32 for a thread with a
                 // finite element.  A thread whose elements are all -inf (masked)
-                // has ct = 0 and exponentials of 0; with the row maximum far
+                // has the reference 0 and exponentials of 0; with the row maximum far
                 // below zero its unclamped factor 2^(32 - cmax) would overflow
                 // and 0 * inf would store NaN.  The clamp keeps it finite.
-                const float f = fast_exp2(fminf(ct + csh, 64.f)) * omuls;
+                const float f = fast_exp2(fminf(csh - nct, 64.f)) * omuls;
 #pragma unroll
                 for (int j = 0; j < VPT; ++j) {
                     float y[EPV];
@@ -498,7 +497,7 @@ __device__ __forceinline__ void row_loop(const RowArgs &a, int c, int grp, const
                 // FP8: 448 * 2^(q K - c) is taken as one exponential, 2^(q K + log2 448 - c),
                 // saving a multiply per element (outputs below 2^-126 of the largest
                 // are 0 either way, far below the smallest e4m3 code)
-                const float cs8 = kLog2Fp8Max - cmax;
+                const float cs8 = ref.out(kLog2Fp8Max, cmax);
                 fresh();
 #pragma unroll
                 for (int j = 0; j < VPT; ++j) {
@@ -506,7 +505,7 @@ __device__ __forceinline__ void row_loop(const RowArgs &a, int c, int grp, const
                     decode<DT>(d0[j], q, 1.f);
 #pragma unroll
                     for (int i = 0; i < EPV; ++i)
-                        y[i] = FP8 ? fast_exp2(fmaf(q[i], K, cs8)) : fast_exp2(fmaf(q[i], K, csh)) * omuls;
+                        y[i] = FP8 ? fast_exp2(fmaf(q[i], K, cs8)) : fast_exp2(fmaf(ref.less(q[i]), K, csh)) * omuls;
                     ST(j, encode<DT>(y, 1.f));
                 }
             }
@@ -515,14 +514,14 @@ __device__ __forceinline__ void row_loop(const RowArgs &a, int c, int grp, const
                 float q[EPV], y[EPV];
                 decode<DT>(LD(l), q, 1.f);
 #pragma unroll
-                for (int i = 0; i < EPV; ++i) y[i] = fast_exp2(fmaf(q[i], K, csh)) * omuls;
+                for (int i = 0; i < EPV; ++i) y[i] = fast_exp2(fmaf(ref.less(q[i]), K, csh)) * omuls;
                 ST(VPT + l, encode<DT>(y, 1.f));
             }
             if (tail) {
                 float q[EPV], y[EPV];
                 decode<DT>(t0, q, 1.f);
 #pragma unroll
-                for (int i = 0; i < EPV; ++i) y[i] = fast_exp2(fmaf(q[i], K, csh)) * omuls;
+                for (int i = 0; i < EPV; ++i) y[i] = fast_exp2(fmaf(ref.less(q[i]), K, csh)) * omuls;
                 store_vec<DT>(orow, tcol, tn, false, encode<DT>(y, 1.f));
             }
         } else if constexpr (OP == OP_LN_FWD || OP == OP_RMS_FWD || OP == OP_LNQ_FWD) {
@@ -1038,8 +1037,9 @@ __device__ __forceinline__ void row_loop(const RowArgs &a, int c, int grp, const
                 decode<DT>(t0, q, 1.f);
                 for (int i = 0; i < tn; ++i) qmax = fmaxf(qmax, q[i]);
             }
-            float st[3] = {qmax == -INFINITY ? -INFINITY : fmaxf(qmax * K, -0x1.fffffep+127f), 0.f, 0.f};  // as in the forward
-            const float ct = qmax == -INFINITY ? 0.f : st[0];
+            float st[3] = {base2_ref(qmax, K), 0.f, 0.f};
+            const FarRef<FP8> ref(st[0], qmax);
+            const float nct = ref.about();
             fresh();
 #pragma unroll
             for (int j = 0; j < VPT; ++j) {
@@ -1049,7 +1049,7 @@ __device__ __forceinline__ void row_loop(const RowArgs &a, int c, int grp, const
                 const bool ok = ok_of(j);
 #pragma unroll
                 for (int i = 0; i < EPV; ++i) {
-                    const float e = ok ? fast_exp2(fmaf(q[i], K, -ct)) : 0.f;
+                    const float e = ok ? fast_exp2(fmaf(ref.less(q[i]), K, nct)) : 0.f;
                     st[1] += e;
                     st[2] = fmaf(e, g[i], st[2]);
                 }
@@ -1060,7 +1060,7 @@ __device__ __forceinline__ void row_loop(const RowArgs &a, int c, int grp, const
                 decode<DT>(t0, q, 1.f);
                 decode<DT>(t1, g, gs);
                 for (int i = 0; i < tn; ++i) {
-                    const float e = fast_exp2(fmaf(q[i], K, -ct));
+                    const float e = fast_exp2(fmaf(ref.less(q[i]), K, nct));
                     st[1] += e;
                     st[2] = fmaf(e, g[i], st[2]);
                 }
@@ -1068,13 +1068,13 @@ __device__ __forceinline__ void row_loop(const RowArgs &a, int c, int grp, const
             row_reduce<3>(st, MergeSoftmax3(), a, row, 0, c, red, xb, parity);
             const float cmax = st[0], inv_s = 1.f / st[1];
             const float cdot = st[2] * inv_s;
-            const float csh = kExpShift - cmax, invs_s = inv_s * kExpUnshift;
+            const float csh = ref.out(kExpShift, cmax), invs_s = inv_s * kExpUnshift;
             auto h = [&](u32x4 xv, u32x4 gv, float *dx) {
                 float q[EPV], g[EPV];
                 decode<DT>(xv, q, 1.f);
                 decode<DT>(gv, g, gs);
 #pragma unroll
-                for (int i = 0; i < EPV; ++i) dx[i] = fast_exp2(fmaf(q[i], K, csh)) * invs_s * (g[i] - cdot);
+                for (int i = 0; i < EPV; ++i) dx[i] = fast_exp2(fmaf(ref.less(q[i]), K, csh)) * invs_s * (g[i] - cdot);
             };
             float oinv = 1.f;
             if constexpr (FP8) {

@@ -170,10 +170,8 @@ __device__ __forceinline__ void stream_softmax_rows(const RowArgs &a, int c, int
         // Exponentials about the wave's maximum c in base-2 units, rounded up to
         // a whole number: 32 - c and the factors 2^(c - c') by which the sums of
         // the waves (and members) are rescaled when merged are then exact (FP8
-        // takes it as it is: its largest code, 448, stands for 2^0).  It is held
-        // finite unless it is -inf itself: rows masked with the type's
-        // lowest value would else add inf * 0.  Elements that are not the lane's
-        // own are -inf (and their dy 0), so they add nothing.
+        // takes it as it is: its largest code, 448, stands for 2^0).  Elements
+        // that are not the lane's own are -inf (and their dy 0), so they add nothing.
         //
         // KEEP: the exponentials stay in registers for the output (the exponential
         // is the dearest instruction here: 2048 x 50257 BF16 k = 4 98 -> 91 us, FP8 4096
@@ -182,11 +180,19 @@ __device__ __forceinline__ void stream_softmax_rows(const RowArgs &a, int c, int
         // registers for them.  Kept BF16 exponentials, and FP32 ones of the
         // backward, are 2^(v + 32), so that results down to 2^-158 of the largest
         // keep their value (device.h).
+        //
+        // A far wave takes its maximum off first (device.h).
+        auto less = [&](float (&q)[EPV], float c, float m) {
+            if (!FP8 && far_ref(c)) {
+#pragma unroll
+                for (int e = 0; e < EPV; ++e) q[e] -= m;
+            }
+        };
         constexpr bool BW = OP == OP_SMXL_BWD, KEEP = V == 4 || (DT == DT_F32 && !BW);
         constexpr float SH = KEEP && (DT == DT_BF16 || BW) ? kExpShift : 0.f;
         constexpr float USH = SH == 0.f ? 1.f : kExpUnshift;
         constexpr unsigned NINF = DT == DT_F32 ? 0xff800000u : 0xff80ff80u;
-        float st[R][S::NS], ct[R];
+        float st[R][S::NS], ct[R], qf[R];
         float ev[KEEP ? R : 1][KEEP ? V * EPV : 1];
 #pragma unroll
         for (int i = 0; i < R; ++i) {
@@ -216,10 +222,11 @@ __device__ __forceinline__ void stream_softmax_rows(const RowArgs &a, int c, int
             }
             opaque<V>(x0[i]);
             qmax = wave_max(qmax);
-            const float cm = FP8 ? qmax * K : ceilf(qmax * kLog2e);
-            st[i][0] = qmax == -INFINITY ? -INFINITY : fmaxf(cm, -0x1.fffffep+127f);
+            st[i][0] = FP8 ? base2_ref(qmax, K) : ceilf(base2_ref(qmax, kLog2e));
             ct[i] = qmax == -INFINITY ? 0.f : st[i][0];
-            const float cs = SH - ct[i];
+            const bool far = !FP8 && far_ref(ct[i]);
+            qf[i] = far ? qmax : 0.f;
+            const float cs = far ? SH : SH - ct[i];
             float s = 0.f, t = 0.f;
 #pragma unroll
             for (int j = 0; j < V; ++j) {
@@ -227,6 +234,7 @@ __device__ __forceinline__ void stream_softmax_rows(const RowArgs &a, int c, int
                 float q[EPV], g[EPV];
                 decode<DT>(x0[i][j], q, 1.f);
                 if constexpr (BW) decode<DT>(x1[i][j], g, 1.f);
+                less(q, ct[i], qf[i]);
                 float x[EPV];
 #pragma unroll
                 for (int e = 0; e < EPV; ++e) x[e] = fast_exp2(fmaf(q[e], FP8 ? K : kLog2e, cs));
@@ -278,7 +286,7 @@ __device__ __forceinline__ void stream_softmax_rows(const RowArgs &a, int c, int
 #pragma unroll
         for (int i = 0; i < R; ++i) {
             const float cmax = st[i][0], inv_s = 1.f / st[i][1];
-            const float csh = kExpShift - cmax, mul = inv_s * kExpUnshift;
+            const float csh = !FP8 && far_ref(ct[i]) ? kExpShift + (ct[i] - cmax) : kExpShift - cmax, mul = inv_s * kExpUnshift;
             const float cdot = BW ? st[i][S::NS - 1] * inv_s : 0.f;
             float f = mul;
             // the clamps keep 0 times the factor 0 for a wave without a finite element
@@ -292,7 +300,7 @@ __device__ __forceinline__ void stream_softmax_rows(const RowArgs &a, int c, int
                 // y = e 2^(ct - c + 32) 2^-64 / s.  A wave whose maximum lies far
                 // below the row's takes the two factors one by one, so that
                 // neither their product nor the result underflows early.
-                const float f1 = fast_exp2(fminf(ct[i] + csh, 64.f));
+                const float f1 = fast_exp2(fminf(ct[i] - cmax + kExpShift, 64.f));
                 f = mul * kExpUnshift;
                 if (f1 < 1.f) {
 #pragma unroll
@@ -304,7 +312,10 @@ __device__ __forceinline__ void stream_softmax_rows(const RowArgs &a, int c, int
 #pragma unroll
             for (int j = 0; j < V; ++j) {
                 float q[EPV], y[EPV], g[EPV];
-                if constexpr (!KEEP) decode<DT>(x0[i][j], q, 1.f);
+                if constexpr (!KEEP) {
+                    decode<DT>(x0[i][j], q, 1.f);
+                    less(q, ct[i], qf[i]);
+                }
                 if constexpr (BW) decode<DT>(x1[i][j], g, 1.f);
 #pragma unroll
                 for (int e = 0; e < EPV; ++e) {

@@ -115,6 +115,7 @@ __global__ __launch_bounds__(BLOCK) void k_twopass(RowArgs a) {
         if constexpr (OP == OP_SOFTMAX_FWD) {
             const float K = (FP8 ? a.s0[row] : 1.f) * kLog2e;
             float st[2] = {-INFINITY, 0.f};  // online base-2 (c, s)
+            float qm = -INFINITY;            // the largest logit so far, of reference c
             stream_row<DT, BLOCK, U, false>(r0, nullptr, N, al0, al1, [&](int64_t, u32x4 v, u32x4, int nv) {
                 float q[EPV];
                 decode<DT>(v, q, 1.f);
@@ -123,26 +124,29 @@ __global__ __launch_bounds__(BLOCK) void k_twopass(RowArgs a) {
                 for (int i = 0; i < EPV; ++i)
                     if (i < nv) bm = fmaxf(bm, q[i]);
                 if (bm == -INFINITY) return;
-                const float cb = bm * K;
-                if (cb > st[0]) {
+                const float cb = base2_ref(bm, K);
+                if (cb > st[0] || (cb == st[0] && bm > qm)) {
+                    qm = bm;
                     st[1] = st[0] == -INFINITY ? 0.f : st[1] * fast_exp2(st[0] - cb);
                     st[0] = cb;
                 }
+                const FarRef<FP8> ref(st[0], qm);
 #pragma unroll
                 for (int i = 0; i < EPV; ++i)
-                    if (i < nv) st[1] += fast_exp2(fmaf(q[i], K, -st[0]));
+                    if (i < nv) st[1] += fast_exp2(fmaf(ref.less(q[i]), K, ref.about()));
             });
+            const FarRef<FP8> ref(st[0], qm);
             block_reduce<NW, 2>(st, MergeSoftmax(), red, parity);
             const float cmax = st[0], inv_s = 1.f / st[1];
             const float omul = FP8 ? kFp8Max : inv_s;
-            const float csh = kExpShift - cmax, omuls = omul * kExpUnshift;
+            const float csh = ref.out(kExpShift, cmax), omuls = omul * kExpUnshift;
             if (FP8 && writer) a.so[row] = inv_s / kFp8Max;
             stream_row<DT, BLOCK, U, true>(r0, nullptr, N, al0, al1, [&](int64_t v, u32x4 d, u32x4, int nv) {
                 if (nv == 0) return;
                 float q[EPV], y[EPV];
                 decode<DT>(d, q, 1.f);
 #pragma unroll
-                for (int i = 0; i < EPV; ++i) y[i] = fast_exp2(fmaf(q[i], K, csh)) * omuls;
+                for (int i = 0; i < EPV; ++i) y[i] = fast_exp2(fmaf(ref.less(q[i]), K, csh)) * omuls;
                 row_store<DT>(orow, v, nv, encode<DT>(y, 1.f));
             });
         } else if constexpr (OP == OP_LN_FWD || OP == OP_RMS_FWD || OP == OP_LN_BWD || OP == OP_RMS_BWD ||
@@ -317,6 +321,7 @@ __global__ __launch_bounds__(BLOCK) void k_twopass(RowArgs a) {
             // streams them again
             const float K = (FP8 ? a.s0[row] : 1.f) * kLog2e, gs = FP8 ? a.s1[row] : 1.f;
             float st[3] = {-INFINITY, 0.f, 0.f};
+            float qm = -INFINITY;  // the largest logit so far, of reference c
             stream_row<DT, BLOCK, U, false>(r0, r1, N, al0, al1, [&](int64_t, u32x4 xv, u32x4 gv, int nv) {
                 float q[EPV], g[EPV];
                 decode<DT>(xv, q, 1.f);
@@ -326,31 +331,34 @@ __global__ __launch_bounds__(BLOCK) void k_twopass(RowArgs a) {
                 for (int i = 0; i < EPV; ++i)
                     if (i < nv) bm = fmaxf(bm, q[i]);
                 if (bm == -INFINITY) return;
-                const float cb = bm * K;
-                if (cb > st[0]) {
+                const float cb = base2_ref(bm, K);
+                if (cb > st[0] || (cb == st[0] && bm > qm)) {
+                    qm = bm;
                     const float f = st[0] == -INFINITY ? 0.f : fast_exp2(st[0] - cb);
                     st[1] *= f;
                     st[2] *= f;
                     st[0] = cb;
                 }
+                const FarRef<FP8> ref(st[0], qm);
 #pragma unroll
                 for (int i = 0; i < EPV; ++i) {
                     if (i < nv) {
-                        const float e = fast_exp2(fmaf(q[i], K, -st[0]));
+                        const float e = fast_exp2(fmaf(ref.less(q[i]), K, ref.about()));
                         st[1] += e;
                         st[2] = fmaf(e, g[i], st[2]);
                     }
                 }
             });
+            const FarRef<FP8> ref(st[0], qm);
             block_reduce<NW, 3>(st, MergeSoftmax3(), red, parity);
             const float cmax = st[0], inv_s = 1.f / st[1], cdot = st[2] * inv_s;
-            const float csh = kExpShift - cmax, invs_s = inv_s * kExpUnshift;
+            const float csh = ref.out(kExpShift, cmax), invs_s = inv_s * kExpUnshift;
             auto h = [&](u32x4 xv, u32x4 gv, float *dx) {
                 float q[EPV], g[EPV];
                 decode<DT>(xv, q, 1.f);
                 decode<DT>(gv, g, gs);
 #pragma unroll
-                for (int i = 0; i < EPV; ++i) dx[i] = fast_exp2(fmaf(q[i], K, csh)) * invs_s * (g[i] - cdot);
+                for (int i = 0; i < EPV; ++i) dx[i] = fast_exp2(fmaf(ref.less(q[i]), K, csh)) * invs_s * (g[i] - cdot);
             };
             float oinv = 1.f;
             if constexpr (FP8) {

@@ -1,14 +1,17 @@
 """Rows with special values in the streaming forms, each against the FP64 result or
 the one-row kernels' of the same row: row scales of 0, rows whose first byte
 is the last of a line, NaN, infinities and lone large elements under LayerNorm,
-constant FP8 rows, FP8 rows of tiny outputs and huge gradients.  A cap on the row groups
+constant FP8 rows, FP8 rows of tiny outputs, huge gradients, logits of any size (in
+every kernel).  A cap on the row groups
 makes a few rows enough for a plan to stream."""
 import pytest
 import torch
 
 from paper_2609_01864_amd import credit as C
 
-from test_stream_gpu import capped  # noqa: F401  (fixture)
+from _cases import ALL_PLANS
+from test_stream_gpu import DTN, capped  # noqa: F401  (fixture)
+from test_stream_rows_gpu import ULP, _bound, _logits_ref
 
 pytestmark = pytest.mark.gpu
 
@@ -190,3 +193,47 @@ def test_logits_backward_of_huge_gradients(capped, dtype, N, k):
         big = dx.float().abs() > 2.0 ** -100
         assert torch.equal(got.double()[big], dx.double()[big] * 2.0 ** e)
     assert capped.check_errors() == C.OK
+
+
+def far_rows(N, td):
+    """Rows masked in part or throughout with values of any size, and others of huge logits."""
+    low = torch.finfo(td).min
+    x = torch.randn((21, N), device="cuda", generator=torch.Generator(device="cuda").manual_seed(N))
+    for r, v in enumerate((-1e4, -3e8, -5e8, -1e9, -3e9, -1e10, -1e30, low, 6e8, 1e10, 3e38)):
+        x[r] = v                                 # constant: uniform
+    x[11, N // 3:] = -1e9                        # masked in part
+    x[12, : (6 * N) // 10] = -1e10
+    x[13, N // 5:] = low
+    x[14] = -1e9                                 # two masks, the larger one's elements share 1
+    x[14, N // 2:] = low
+    x[15] = -1e30
+    x[15, ::3] = -1e10
+    x[16, N // 4] = 1e10                         # one element is all there is
+    x[17] *= 1e9
+    x[18] *= 1e30
+    x[19] = low
+    x[19, N - 1] = -1e30
+    return x.to(td)                              # row 20: ordinary
+
+
+@pytest.mark.parametrize("form", ["one_row", "streaming"])
+@pytest.mark.parametrize("N", [17, 1000, 5001, 40000, 70001])
+@pytest.mark.parametrize("dtype", ["f32", "bf16"])
+def test_softmax_of_logits_of_any_size(capped, gpu_handle, dtype, N, form):
+    h = capped if form == "streaming" else gpu_handle
+    x = far_rows(N, TD[dtype])
+    dy = torch.randn(x.shape, device="cuda").to(x.dtype)
+    want = torch.softmax(x.double(), 1)
+    ref, yy, g = _logits_ref(x, dy)
+    assert bool(torch.isfinite(want).all())
+    for v, k in ALL_PLANS:
+        p = C.plan(v, k)
+        if h.plan_legal(C.SOFTMAX, C.FWD, DTN[dtype], 21, N, p):
+            print(f"[special] softmax of any logits {form} {dtype} {N} {p}", flush=True)
+            y, _ = C.softmax_fwd(x, p=p, h=h)
+            tol = 2e-6 if dtype == "f32" else ULP["bf16"] * want + 2.0 ** -132
+            assert bool(((y.double() - want).abs() <= tol).all()), p
+        if h.plan_legal(C.SOFTMAX_LOGITS, C.BWD, DTN[dtype], 21, N, p):
+            dx = C.softmax_logits_bwd(x, dy, p=p, h=h)[0].double()
+            assert bool(((dx - ref).abs() <= _bound(dtype, yy, g) + 2.0 ** -132).all()), p
+    assert h.check_errors() == C.OK
