@@ -125,8 +125,9 @@ typedef CREDIT_ENUM {
     CREDIT_SEL_EXHAUSTIVE = 2, /* time every legal plan, keep the fastest           */
     CREDIT_SEL_FIXED = 3,      /* resident if it fits, else smallest legal k, else two-pass */
     CREDIT_SEL_PEAK = 4,       /* Eq. (9) with the baseline priced at calibrated copy bandwidth */
-    CREDIT_SEL_LEARNED_TIMED = 5 /* the MLP's two best legal plans, each timed once (cold,
-                                    median of 7), the faster kept; falls back to ANALYTIC */
+    CREDIT_SEL_LEARNED_TIMED = 5 /* the MLP's two best legal plans, and the one that a call
+                                    without a plan prefers to them, each timed once (cold,
+                                    median of 7), the fastest kept; falls back to ANALYTIC */
 } credit_selector_t;
 
 /* variant and split factor; k == 1 for CREDIT_TWO_PASS and CREDIT_ROW_RESIDENT,

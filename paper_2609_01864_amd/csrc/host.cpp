@@ -1462,9 +1462,12 @@ credit_status_t exhaustive_pick(credit_handle_t h, int k_op, int dt, int64_t M, 
 constexpr float kTieLogit = 0.5f;
 // The network's best legal plan -- among the legal plans whose logits lie
 // within kTieLogit of the best, the one moving the fewest bytes -- or with
-// `timed` its two best legal plans, each timed (cold cache, median of 7),
-// keeping the faster: the model as a screen that narrows the search, the
-// final choice by measurement.
+// `timed` its two best legal plans and the one that a call without a plan
+// prefers to them (stream_default), each timed (cold cache, median of 7),
+// keeping the fastest: the model as a screen that narrows the search, the
+// final choice by measurement.  (The network's training predates the streaming
+// forms: FP8 LayerNorm 1024 x 262144 its two best take 305 and 251 us, the
+// default plan 155.)
 credit_status_t learned_pick(credit_handle_t h, int k_op, int dt, int64_t M, int64_t N, bool timed,
                              credit_plan_t *out, float *pred) {
     float f[CREDIT_NUM_FEATURES], logits[CREDIT_NUM_PLANS];
@@ -1492,14 +1495,24 @@ credit_status_t learned_pick(credit_handle_t h, int k_op, int dt, int64_t M, int
         return CREDIT_OK;
     }
     *out = class_plan(best);
-    if (second < 0) return CREDIT_OK;
-    float t1 = 0.f, t2 = 0.f;
-    st = time_plan(h, k_op, dt, M, N, class_plan(best), 7, 1, &t1);
-    if (st != CREDIT_OK) return st;
-    st = time_plan(h, k_op, dt, M, N, class_plan(second), 7, 1, &t2);
-    if (st != CREDIT_OK) return st;
-    if (t2 < t1) *out = class_plan(second);
-    if (pred) *pred = std::min(t1, t2);
+    credit_plan_t tries[3] = {class_plan(best)}, d;
+    int n = 1;
+    if (second >= 0) tries[n++] = class_plan(second);
+    if (stream_default(h, k_op, dt, M, N, &d) &&
+        std::none_of(tries, tries + n, [&](const credit_plan_t &p) { return p.variant == d.variant && p.k == d.k; }))
+        tries[n++] = d;
+    if (n == 1) return CREDIT_OK;
+    float least = INFINITY;
+    for (int i = 0; i < n; ++i) {
+        float t = 0.f;
+        st = time_plan(h, k_op, dt, M, N, tries[i], 7, 1, &t);
+        if (st != CREDIT_OK) return st;
+        if (t < least) {
+            least = t;
+            *out = tries[i];
+        }
+    }
+    if (pred) *pred = least;
     return CREDIT_OK;
 }
 
