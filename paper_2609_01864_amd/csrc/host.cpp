@@ -2686,6 +2686,7 @@ credit_status_t credit_set_option(credit_handle_t h, credit_option_t opt, int64_
         for (int r : kMrRows) ok |= value == r;
         if (!ok) return CREDIT_ERR_INVALID_ARG;
         h->rows_opt = (int)value;
+        h->plan_cache.clear();  // it decides which plans stream, and so the default one
         return CREDIT_OK;
     }
     }

@@ -1,6 +1,10 @@
 """The plan of calls without one: the timed learned selector never leaves such calls
-slower than it found them."""
+slower than it found them, and it does not depend on calls made under other
+options."""
+import json
+
 import pytest
+import torch
 
 from paper_2609_01864_amd import credit as C
 
@@ -23,3 +27,30 @@ def test_timed_selector_times_the_plan_of_a_call_without_one(lib_built):
         assert pred <= 1.2 * best and p.as_tuple() not in two
     finally:
         h.close()
+
+
+def test_default_plan_follows_the_rows_option(lib_built, monkeypatch, tmp_path):
+    # with the rows per workgroup set no norm forward streams, so what a call
+    # picked before is not what it would pick now
+    path = tmp_path / "calls.jsonl"
+    monkeypatch.setenv("CREDIT_LOG", str(path))
+    M, N = 4096, 20000
+    q = (torch.randn((M, N), device="cuda") * 50).to(torch.float8_e4m3fn)
+    s = torch.rand(M, device="cuda") * 1e-2 + 1e-3
+    g, b = torch.rand(N, device="cuda"), torch.rand(N, device="cuda")
+    used, fresh = C.Handle(0), C.Handle(0)
+    try:
+        print("[default plan] rows option", flush=True)
+        C.layernorm_fwd(q, g, b, x_scale=s, h=used)
+        used.set_option(C.OPT_ROWS, 1)
+        fresh.set_option(C.OPT_ROWS, 1)
+        C.layernorm_fwd(q, g, b, x_scale=s, h=used)
+        C.layernorm_fwd(q, g, b, x_scale=s, h=fresh)
+        used.set_option(C.OPT_ROWS, 0)
+        C.layernorm_fwd(q, g, b, x_scale=s, h=used)
+        torch.cuda.synchronize()
+    finally:
+        used.close()
+        fresh.close()
+    plans = [json.loads(line)["plan"] for line in path.read_text().splitlines()]
+    assert plans[0] != plans[1] and plans[1] == plans[2] and plans[3] == plans[0]
