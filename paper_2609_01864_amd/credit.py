@@ -347,9 +347,12 @@ class Handle:
             check(lib().credit_create(self.device, ctypes.byref(p)), "credit_create")
         self.ptr = p
         self._ws = {}
-        # workspace bytes by (op, direction, dtype, M, N, plan): a function of
-        # the shape and the handle's options only, so set_option clears it
+        # workspace bytes by (generation, op, direction, dtype, M, N, plan): a
+        # function of the shape and the handle's options only.  set_option begins a
+        # new generation, so a size that another thread worked out before the
+        # option changed is not found after it, whenever it is entered
         self._sizes = {}
+        self._generation = 0
         # workspaces replaced by a larger one stay allocated until the handle
         # goes away: a launch recorded into a HIP graph keeps the raw address of
         # the workspace it was captured with, and replaying it must not write
@@ -375,8 +378,11 @@ class Handle:
         check(lib().credit_set_selector(self.ptr, sel), "credit_set_selector")
 
     def set_option(self, opt: int, value: int) -> None:
-        self._sizes.clear()
-        check(lib().credit_set_option(self.ptr, opt, int(value)), "credit_set_option")
+        try:
+            check(lib().credit_set_option(self.ptr, opt, int(value)), "credit_set_option")
+        finally:
+            self._generation += 1
+            self._sizes.clear()
 
     def load_model(self, path: str) -> int:
         s = lib().credit_load_model(self.ptr, path.encode())
@@ -499,7 +505,7 @@ class Handle:
 
     def _call_ws(self, op, direction, dtype, M, N, p, stream):
         """The stream's workspace, large enough for the call."""
-        key = (op, direction, dtype, M, N, None if p is None else (p.variant, p.k))
+        key = (self._generation, op, direction, dtype, M, N, None if p is None else (p.variant, p.k))
         n = self._sizes.get(key)
         if n is None:
             n = self.workspace_size(op, direction, dtype, M, N, p) if M > 0 else 0
