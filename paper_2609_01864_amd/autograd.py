@@ -21,6 +21,12 @@ def _as(t, like):
     return t if t.shape == like.shape else t.view(like.shape)
 
 
+def _out(y, x):
+    """An operator's rows in the shape of its input -- and of its kind, for a
+    subclass of Tensor."""
+    return _as(y, x) if type(x) in (torch.Tensor, torch.nn.Parameter) else y.view_as(x)
+
+
 def _grad_rows(dy, dtype):
     """The incoming gradient as contiguous rows of the operator's dtype."""
     if dy.dtype != dtype:
@@ -35,7 +41,7 @@ class SoftmaxFn(torch.autograd.Function):
         y, _ = C.softmax_fwd(x2, p=plan)
         ctx.save_for_backward(y)
         ctx.plan_bwd = None
-        return _as(y, x)
+        return _out(y, x)
 
     @staticmethod
     def backward(ctx, dy):
@@ -53,7 +59,7 @@ class SoftmaxLogitsFn(torch.autograd.Function):
         x2 = _rows(x.contiguous())
         y, _ = C.softmax_fwd(x2, p=plan)
         ctx.save_for_backward(x2)
-        return _as(y, x)
+        return _out(y, x)
 
     @staticmethod
     def backward(ctx, dy):
@@ -69,7 +75,7 @@ class LayerNormFn(torch.autograd.Function):
         y, _, mean, rstd = C.layernorm_fwd(x2, gamma.contiguous(), beta.contiguous(), eps, p=plan)
         ctx.save_for_backward(x2, gamma, mean, rstd)
         ctx.eps = eps
-        return _as(y, x)
+        return _out(y, x)
 
     @staticmethod
     def backward(ctx, dy):
@@ -87,7 +93,7 @@ class RMSNormFn(torch.autograd.Function):
         y, _, rstd = C.rmsnorm_fwd(x2, gamma.contiguous(), eps, p=plan)
         ctx.save_for_backward(x2, gamma, rstd)
         ctx.eps = eps
-        return _as(y, x)
+        return _out(y, x)
 
     @staticmethod
     def backward(ctx, dy):

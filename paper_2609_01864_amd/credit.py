@@ -545,7 +545,10 @@ def handle(device: Optional[int] = None) -> Handle:
 
 
 def _empty_like_out(x):
-    return _torch_mod.empty_like(x, memory_format=_torch_mod.contiguous_format)
+    """A plain packed tensor of x's shape, dtype and device."""
+    if type(x) is _torch_mod.Tensor:  # the shorter call, which a subclass would answer with its own kind
+        return _torch_mod.empty_like(x, memory_format=_torch_mod.contiguous_format)
+    return _torch_mod.empty(x.shape, dtype=x.dtype, device=x.device)
 
 
 def _scale_out(x, M):

@@ -1,6 +1,10 @@
-"""The binding's own state, without a device: the workspace sizes a handle keeps."""
+"""The binding's own state, without a device: the workspace sizes a handle keeps,
+and the kinds of tensors it makes."""
 from types import SimpleNamespace
 
+import torch
+
+from paper_2609_01864_amd import autograd as A
 from paper_2609_01864_amd import credit as C
 
 
@@ -52,3 +56,20 @@ def test_size_worked_out_before_an_option_changed(monkeypatch):
     s.during = lambda: (setattr(s, "during", lambda: None), s.h.set_option(C.OPT_ROWS, 2))
     call()
     assert call() == 102
+
+
+class Kind(torch.Tensor):
+    pass
+
+
+def test_results_of_tensor_subclasses():
+    # the operators make plain tensors; the autograd functions return the kind
+    # of their input, as they do for one of more than two dimensions
+    C.io_dtype(torch.empty(0))  # (the binding's torch)
+    for x in (torch.ones(2, 3), torch.nn.Parameter(torch.ones(2, 3)), torch.ones(2, 3).as_subclass(Kind)):
+        y = C._empty_like_out(x)
+        assert type(y) is torch.Tensor and y.shape == (2, 3) and y.dtype == x.dtype and y.is_contiguous()
+        want = Kind if type(x) is Kind else torch.Tensor
+        assert type(A._out(y, x)) is want and type(A._out(y, x.view(1, 2, 3))) is want
+    t = torch.ones(3, 2).t()
+    assert C._empty_like_out(t).is_contiguous()
