@@ -110,20 +110,14 @@ def device_identity(torch):
 
 def kernel_symbol(C, h, op_num, dt_num, M, N, p):
     """Demangled name prefix and grid (work-items) of the launch of plan p."""
-    g = h.geometry(op_num, C.FWD if op_num < 3 else C.BWD, dt_num, M, N, p)
-    kop = op_num
-    if p.variant == C.TWO_PASS:
-        return f"void credit::k_twopass<{kop}, {dt_num}, {g['block']}, 4>", g["grid"] * g["block"]
-    one = C.plan_geometry(None, op_num, C.FWD if op_num < 3 else C.BWD, dt_num, M, N, p)
-    if g["block"] != one["block"] or g["vpt"] != one["vpt"]:  # the streaming form
-        if dt_num == C.FP8 and kop == 1:
-            return "void credit::k_stream_ln_fp8<", g["grid"] * g["block"]
-        name = "k_stream_softmax" if kop == 0 else "k_stream"
-        return f"void credit::{name}<{kop}, {dt_num}, {g['vpt']}, {g['rows']}, ", g["grid"] * g["block"]
-    if g["rows"] > 1:  # the multi-row norm forward
-        return f"void credit::k_multirow<{kop}, {dt_num}, {g['vpt']}, {g['rows']}>", g["grid"] * g["block"]
+    kop, d = op_num, C.FWD if op_num < 3 else C.BWD
+    g, name = h.geometry(op_num, d, dt_num, M, N, p), h.kernel(op_num, d, dt_num, M, N, p)
     reg = min(g["vpt"], 32)  # slices past 32 vectors per thread keep the rest in LDS
-    return f"void credit::k_resident<{kop}, {dt_num}, {reg}, {g['vpt'] - reg}>", g["grid"] * g["block"]
+    args = {"k_twopass": f"{kop}, {dt_num}, {g['block']}, ", "k_resident": f"{kop}, {dt_num}, {reg}, {g['vpt'] - reg}>",
+            "k_multirow": f"{kop}, {dt_num}, {g['vpt']}, {g['rows']}>", "k_stream_ln_fp8": "",
+            "k_stream_quant": f"{dt_num}, {g['vpt']}, {g['rows']}, "}
+    stream = f"{kop}, {dt_num}, {g['vpt']}, {g['rows']}, "  # k_stream, k_stream_softmax
+    return f"void credit::{name}<{args.get(name, stream)}", g["grid"] * g["block"]
 
 
 def precision_inputs(M, N, seed, dev):

@@ -543,6 +543,14 @@ credit_status_t credit_plan_geometry(credit_handle_t h, credit_op_t op, credit_d
                                      const credit_plan_t *plan, int32_t *grid, int32_t *block,
                                      int32_t *vpt, int32_t *per_cu, int32_t *rows);
 
+/* The kernel that does a plan's row work: "k_twopass", "k_resident" (one row per
+ * workgroup), "k_multirow", or one of the streaming form, "k_stream",
+ * "k_stream_softmax", "k_stream_ln_fp8", "k_stream_quant" -- the geometry alone does
+ * not tell the forms apart.  *name is a static string.  Host-only; with h ==
+ * NULL as credit_plan_geometry. */
+credit_status_t credit_plan_kernel(credit_handle_t h, credit_op_t op, credit_dir_t dir, credit_dtype_t dt,
+                                   int64_t M, int64_t N, const credit_plan_t *plan, const char **name);
+
 /* Resources of the row-resident / split-row kernel instance of (op, dir, dt)
  * that holds `vpt` 16-byte vectors per thread per tensor (vpt in
  * {1, 2, 4, 8, 12, 16, 24, 32}, up to the operator's register capacity, and

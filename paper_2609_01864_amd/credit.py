@@ -151,6 +151,7 @@ _SIGS = {
     "credit_probe_primitives": ([_P, _S, ctypes.POINTER(Primitives)], _S),
     "credit_plan_geometry": ([_P, _S, _S, _S, _I64, _I64, _PP, ctypes.POINTER(_I32), ctypes.POINTER(_I32),
                               ctypes.POINTER(_I32), ctypes.POINTER(_I32), ctypes.POINTER(_I32)], _S),
+    "credit_plan_kernel": ([_P, _S, _S, _S, _I64, _I64, _PP, ctypes.POINTER(ctypes.c_char_p)], _S),
     "credit_instance_info": ([_P, _S, _S, _S, _I32, _I32, ctypes.POINTER(Instance)], _S),
 }
 
@@ -234,6 +235,17 @@ def plan_geometry(handle, op, direction, dtype, M, N, p: Plan):
         return None
     check(s, "credit_plan_geometry")
     return {"grid": g.value, "block": b.value, "vpt": v.value, "per_cu": o.value, "rows": r.value}
+
+
+def plan_kernel(handle, op, direction, dtype, M, N, p: Plan) -> Optional[str]:
+    """Name of the kernel that does the plan's row work (None: illegal plan)."""
+    name = ctypes.c_char_p()
+    h = handle.ptr if handle is not None else None
+    s = lib().credit_plan_kernel(h, op, direction, dtype, M, N, ctypes.byref(p), ctypes.byref(name))
+    if s == ERR_UNSUPPORTED:
+        return None
+    check(s, "credit_plan_kernel")
+    return name.value.decode()
 
 
 def instance_info(handle, op, direction, dtype, vpt: int, rows: int = 1):
@@ -415,6 +427,9 @@ class Handle:
 
     def geometry(self, op, direction, dtype, M, N, p: Plan):
         return plan_geometry(self, op, direction, dtype, M, N, p)
+
+    def kernel(self, op, direction, dtype, M, N, p: Plan) -> Optional[str]:
+        return plan_kernel(self, op, direction, dtype, M, N, p)
 
     # -- timing
     def time_plan(self, op, direction, dtype, M, N, p: Plan, reps: int = 15, flush: bool = True) -> float:

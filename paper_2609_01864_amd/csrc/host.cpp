@@ -2004,6 +2004,32 @@ credit_status_t credit_plan_geometry(credit_handle_t h, credit_op_t op, credit_d
     return CREDIT_OK;
 }
 
+credit_status_t credit_plan_kernel(credit_handle_t h, credit_op_t op, credit_dir_t dir, credit_dtype_t dt, int64_t M,
+                                   int64_t N, const credit_plan_t *plan, const char **name) {
+    if (!plan || !name || !valid_enum(op, dir, dt) || M < 0 || N <= 0) return CREDIT_ERR_INVALID_ARG;
+    Launch L;
+    const int k_op = kop(op, dir);
+    credit_status_t st;
+    try {
+        if (h) {
+            std::lock_guard<std::recursive_mutex> g(h->lock);
+            st = resolve(h, k_op, dt, M, N, *plan, false, L);
+        } else {
+            st = resolve(nullptr, k_op, dt, M, N, *plan, false, L);
+        }
+    } catch (...) {
+        return CREDIT_ERR_HIP;
+    }
+    if (st != CREDIT_OK) return st;
+    *name = L.variant == CREDIT_TWO_PASS ? "k_twopass"
+            : !L.stream                  ? (L.rows > 1 ? "k_multirow" : "k_resident")
+            : softmax_stream(k_op)       ? "k_stream_softmax"
+            : is_quant(k_op)             ? "k_stream_quant"
+            : dt == CREDIT_FP8_E4M3      ? "k_stream_ln_fp8"
+                                         : "k_stream";
+    return CREDIT_OK;
+}
+
 credit_status_t credit_select(credit_handle_t h, credit_op_t op, credit_dir_t dir, credit_dtype_t dt, int64_t M,
                               int64_t N, credit_plan_t *out, float *predicted_us) {
     if (!h || !out || !valid_enum(op, dir, dt) || M <= 0 || N <= 0) return CREDIT_ERR_INVALID_ARG;
