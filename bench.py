@@ -11,7 +11,9 @@ from a cache warmed by the previous call.
 Prints one JSON line: aggregate algorithmic GB/s over the timed steps, the
 roofline of the dominant kernel (HIP events on the launch stream), the CPU
 oracle timed on a bounded sample, and per-shape plan regret against
-exhaustive timing.
+exhaustive timing.  The record behind it (the times of every plan, the precision
+and backward workloads, the evaluation suite, the calibration primitives) goes to
+stderr, and to a file with --details: with them the line is over 20 KB long.
 """
 from __future__ import annotations
 
@@ -106,6 +108,14 @@ def device_identity(torch):
     return {"name": pr.name, "arch": pr.gcnArchName, "cus": pr.multi_processor_count,
             "pci": f"{pr.pci_domain_id:04x}:{pr.pci_bus_id:02x}:{pr.pci_device_id:02x}", "uuid": str(pr.uuid),
             "total_memory_gib": round(pr.total_memory / 2 ** 30, 1)}
+
+
+def result_line(full):
+    """The record's part that the result line carries: a few KB at most."""
+    line = {k: v for k, v in full.items() if k not in ("per_shape", "forms", "paper_suite", "primitives")}
+    keep = ("op", "N", "plan", "us", "gbps", "frac", "best_plan", "regret", "regret_noise_aware")
+    line["per_shape"] = [{k: r[k] for k in keep if k in r} for r in full["per_shape"]]
+    return line
 
 
 def kernel_symbol(C, h, op_num, dt_num, M, N, p):
@@ -479,6 +489,7 @@ def main():
                          "with the precision workload's rows, timed alone: the launch sequence a counter "
                          "profile of that kernel runs under")
     ap.add_argument("--plan", default=None, help="--single: plan as variant:k (default: the selector's)")
+    ap.add_argument("--details", default=None, metavar="FILE", help="also write the complete record, as JSON")
     ap.add_argument("--dominant", default=None, metavar="OP:N",
                     help="report the roofline for this shape (e.g. layernorm_fwd:524288) instead of the longest "
                          "launch, so that counter runs of two launches of nearly equal length name the same kernel")
@@ -702,7 +713,11 @@ def main():
         "source_hash": source_hash(),
         "device": device_identity(torch),
     }
-    print(json.dumps(out), flush=True)
+    log("details " + json.dumps(out))
+    if args.details:
+        with open(args.details, "w") as f:
+            json.dump(out, f, indent=1)
+    print(json.dumps(result_line(out)), flush=True)
 
 
 if __name__ == "__main__":
