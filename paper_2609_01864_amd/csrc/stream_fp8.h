@@ -300,8 +300,10 @@ __device__ __forceinline__ void stream_ln_fp8_rows(const RowArgs &a, int c, int 
         const float mw = fold(s1, FoldSum()) * inv_held;
         float m2 = fold(s2, FoldSum()) - held * mw * mw, mean = mw;
         // Where the mean is large beside the spread the difference of the two
-        // has lost digits: moments about the wave's mean instead.
-        if (__builtin_amdgcn_ballot_w64(!(held * mw * mw <= 2.f * m2)) != 0) {
+        // has lost digits: moments about the wave's mean instead, for those rows
+        // (a row's result is not to depend on the others of its round).
+        const bool lost = !(held * mw * mw <= 2.f * m2);
+        if (__builtin_amdgcn_ballot_w64(lost) != 0) {
             opaque<R>(n.x);
 #pragma unroll
             for (int i = 0; i < R; ++i) {
@@ -318,8 +320,8 @@ __device__ __forceinline__ void stream_ln_fp8_rows(const RowArgs &a, int c, int 
                 keep_order(s1[i], s2[i]);
             }
             const float f1 = fold(s1, FoldSum()), f2 = fold(s2, FoldSum()), r = f1 * inv_held;
-            mean += r;
-            m2 = f2 - f1 * r;
+            mean = lost ? mean + r : mean;
+            m2 = lost ? f2 - f1 * r : m2;
         }
         st[0] = held;
         st[1] = held > 0.f ? mean : 0.f;

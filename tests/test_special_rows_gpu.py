@@ -2,7 +2,7 @@
 the one-row kernels' of the same row: row scales of 0, rows whose first byte
 is the last of a line, NaN, infinities and lone large elements under LayerNorm,
 constant FP8 rows, FP8 rows of tiny outputs, huge gradients, logits of any size (in
-every kernel).  A cap on the row groups
+every kernel), and FP8 rows beside rows of another kind.  A cap on the row groups
 makes a few rows enough for a plan to stream."""
 import pytest
 import torch
@@ -237,3 +237,23 @@ def test_softmax_of_logits_of_any_size(capped, gpu_handle, dtype, N, form):
             dx = C.softmax_logits_bwd(x, dy, p=p, h=h)[0].double()
             assert bool(((dx - ref).abs() <= _bound(dtype, yy, g) + 2.0 ** -132).all()), p
     assert h.check_errors() == C.OK
+
+
+@pytest.mark.parametrize("N,k", [(1000, 1), (5001, 1), (16384, 1), (20001, 8)])
+def test_fp8_layernorm_rows_do_not_depend_on_each_other(capped, N, k):
+    # four rows share a round; one whose spread is small beside its mean takes
+    # its moments in a second pass
+    M = 32
+    p = C.plan("split", k) if k > 1 else C.plan("resident")
+    print(f"[special] fp8 layernorm neighbours {M} x {N} {p}", flush=True)
+    q = (torch.randn((M, N), device="cuda") * 40 + 15).clamp(-448, 448).to(torch.float8_e4m3fn)
+    s = torch.rand(M, device="cuda") + 0.5
+    g, b = torch.rand(N, device="cuda") + 0.5, torch.randn(N, device="cuda")
+    want = C.layernorm_fwd(q, g, b, x_scale=s, p=p, h=capped)
+    q[1::4] = 416.0
+    q[1::4, ::7] = 448.0
+    got = C.layernorm_fwd(q, g, b, x_scale=s, p=p, h=capped)
+    keep = [r for r in range(M) if r % 4 != 1]
+    for a, e in zip(got, want):
+        assert torch.equal(a[keep].view(torch.uint8), e[keep].view(torch.uint8))
+    assert capped.check_errors() == C.OK
