@@ -39,13 +39,14 @@ constexpr float kExpUnshift = 0x1p-32f;
 // or more there: 32 - c loses the shift above, and what q log2(e) - c rounds to is
 // as large as an exponent, so a row masked throughout with -1e9 (uniform) came out
 // as zeros and one masked with -1e10 or the type's lowest value as NaN.  A thread (in
-// the streaming kernels a wave) whose c is far subtracts its maximum m from q
-// before the multiplication and takes c as 0 in the exponent; c itself, held
-// finite, only ranks it among the others.  (Two whose maxima are neighbouring FP32
-// numbers may have the same c, and then count alike.)  FP8 codes do not reach it.
-// One-row BF16 rows kept in LDS pay 5% for the subtraction (1024 x 131072 139 ->
-// 146 us), two-pass ones 2.5%, the others 0 to 2%; a branch around it saves the
-// register slots nothing and costs them occupancy.
+// the streaming kernels a wave) whose c is far takes its maximum m off its elements,
+// held as they are, before the multiplication and takes c as 0 in the exponent; c
+// itself, held finite, only ranks it among the others.  (Two whose maxima are
+// neighbouring FP32 numbers may have the same c, and then count alike.)  A two-pass
+// row that is far is done over, in three passes.  FP8 codes do not reach it.  Other
+// rows pay for the test alone: 0 to 2% at the sizes where each kernel is the fastest;
+// short rows under an explicit two-pass plan, which no rule gives them, up to 40%
+// (FP32 12762 x 1579 52 -> 68 us, one-row 33; BF16 8979 x 940 34 -> 45).
 constexpr float kFar = 0x1p29f, kFltMax = 0x1.fffffep+127f;
 __device__ __forceinline__ bool far_ref(float c) { return fabsf(c) >= kFar; }
 __device__ __forceinline__ float base2_ref(float qmax, float K) {

@@ -435,6 +435,32 @@ __device__ __forceinline__ void row_loop(const RowArgs &a, int c, int grp, const
             float st[2] = {base2_ref(qmax, K), 0.f};
             const FarRef<FP8> ref(st[0], qmax);
             const float nct = ref.about();
+            // Far threads (device.h) take their maximum off: FP32 elements as they are
+            // used (their exponentials are taken once; 578 x 33859 39 us, 43 the other
+            // way), BF16 ones where they are held -- a difference is 0 or so large that
+            // any rounding will do -- before the two passes over them.  The largest
+            // slices take both passes' subtractions (1024 x 131072 139 -> 146 us): with
+            // a second loop over their LDS slots the compiler (ROCm 7.2) copies a
+            // store's offset to an accumulation register where only the tail's owner
+            // is active, and the others store anywhere.
+            constexpr bool SUB = DT == DT_F32 || L > 16;
+            auto off = [&](float q) -> float { return SUB ? ref.less(q) : q; };
+            if (!FP8 && !SUB && __builtin_expect(__builtin_amdgcn_ballot_w64(ref.m != 0.f) != 0, 0)) {
+                auto less = [&](u32x4 &d) {
+                    float q[EPV];
+                    asm volatile("" : "+v"(d));
+                    decode<DT>(d, q, 1.f);
+#pragma unroll
+                    for (int i = 0; i < EPV; ++i) q[i] -= ref.m;
+                    d = encode<DT>(q, 1.f);
+                    asm volatile("" : "+v"(d));
+                };
+#pragma unroll
+                for (int j = 0; j < VPT; ++j) less(d0[j]);
+#pragma unroll
+                for (int l = 0; l < L; ++l) less(lds[l * kBlock + tid]);
+                less(t0);
+            }
             fresh();
 #pragma unroll
             for (int j = 0; j < VPT; ++j) {
@@ -443,7 +469,7 @@ __device__ __forceinline__ void row_loop(const RowArgs &a, int c, int grp, const
                 const bool ok = ok_of(j);
 #pragma unroll
                 for (int i = 0; i < EPV; ++i) {
-                    ev[i] = fast_exp2(fmaf(ref.less(EC ? ec[j * EPV + i] : q[i]), K, nct));
+                    ev[i] = fast_exp2(fmaf(off(EC ? ec[j * EPV + i] : q[i]), K, nct));
                     if constexpr (EC) ec[j * EPV + i] = ev[i];
                     st[1] += ok ? ev[i] : 0.f;
                 }
@@ -458,13 +484,13 @@ __device__ __forceinline__ void row_loop(const RowArgs &a, int c, int grp, const
                 decode<DT>(LD(l), q, 1.f);
                 const bool ok = ok_of(VPT + l);
 #pragma unroll
-                for (int i = 0; i < EPV; ++i) st[1] += ok ? fast_exp2(fmaf(ref.less(q[i]), K, nct)) : 0.f;
+                for (int i = 0; i < EPV; ++i) st[1] += ok ? fast_exp2(fmaf(off(q[i]), K, nct)) : 0.f;
                 keep_order(st[1]);
             }
             if (tail) {
                 float q[EPV];
                 decode<DT>(t0, q, 1.f);
-                for (int i = 0; i < tn; ++i) st[1] += fast_exp2(fmaf(ref.less(q[i]), K, nct));
+                for (int i = 0; i < tn; ++i) st[1] += fast_exp2(fmaf(off(q[i]), K, nct));
             }
             row_reduce<2>(st, MergeSoftmax(), a, row, 0, c, red, xb, parity);
             const float cmax = st[0];
@@ -505,7 +531,7 @@ __device__ __forceinline__ void row_loop(const RowArgs &a, int c, int grp, const
                     decode<DT>(d0[j], q, 1.f);
 #pragma unroll
                     for (int i = 0; i < EPV; ++i)
-                        y[i] = FP8 ? fast_exp2(fmaf(q[i], K, cs8)) : fast_exp2(fmaf(ref.less(q[i]), K, csh)) * omuls;
+                        y[i] = FP8 ? fast_exp2(fmaf(q[i], K, cs8)) : fast_exp2(fmaf(off(q[i]), K, csh)) * omuls;
                     ST(j, encode<DT>(y, 1.f));
                 }
             }
@@ -514,14 +540,14 @@ __device__ __forceinline__ void row_loop(const RowArgs &a, int c, int grp, const
                 float q[EPV], y[EPV];
                 decode<DT>(LD(l), q, 1.f);
 #pragma unroll
-                for (int i = 0; i < EPV; ++i) y[i] = fast_exp2(fmaf(ref.less(q[i]), K, csh)) * omuls;
+                for (int i = 0; i < EPV; ++i) y[i] = fast_exp2(fmaf(off(q[i]), K, csh)) * omuls;
                 ST(VPT + l, encode<DT>(y, 1.f));
             }
             if (tail) {
                 float q[EPV], y[EPV];
                 decode<DT>(t0, q, 1.f);
 #pragma unroll
-                for (int i = 0; i < EPV; ++i) y[i] = fast_exp2(fmaf(ref.less(q[i]), K, csh)) * omuls;
+                for (int i = 0; i < EPV; ++i) y[i] = fast_exp2(fmaf(off(q[i]), K, csh)) * omuls;
                 store_vec<DT>(orow, tcol, tn, false, encode<DT>(y, 1.f));
             }
         } else if constexpr (OP == OP_LN_FWD || OP == OP_RMS_FWD || OP == OP_LNQ_FWD) {
@@ -1040,6 +1066,22 @@ __device__ __forceinline__ void row_loop(const RowArgs &a, int c, int grp, const
             float st[3] = {base2_ref(qmax, K), 0.f, 0.f};
             const FarRef<FP8> ref(st[0], qmax);
             const float nct = ref.about();
+            if (!FP8 && __builtin_expect(__builtin_amdgcn_ballot_w64(ref.m != 0.f) != 0, 0)) {
+                // far threads take their maximum off their elements where they
+                // are: a difference is 0 or so large that any rounding will do
+                auto less = [&](u32x4 &d) {
+                    float q[EPV];
+                    asm volatile("" : "+v"(d));
+                    decode<DT>(d, q, 1.f);
+#pragma unroll
+                    for (int i = 0; i < EPV; ++i) q[i] -= ref.m;
+                    d = encode<DT>(q, 1.f);
+                    asm volatile("" : "+v"(d));
+                };
+#pragma unroll
+                for (int j = 0; j < VPT; ++j) less(d0[j]);
+                less(t0);
+            }
             fresh();
 #pragma unroll
             for (int j = 0; j < VPT; ++j) {
@@ -1049,7 +1091,7 @@ __device__ __forceinline__ void row_loop(const RowArgs &a, int c, int grp, const
                 const bool ok = ok_of(j);
 #pragma unroll
                 for (int i = 0; i < EPV; ++i) {
-                    const float e = ok ? fast_exp2(fmaf(ref.less(q[i]), K, nct)) : 0.f;
+                    const float e = ok ? fast_exp2(fmaf(q[i], K, nct)) : 0.f;
                     st[1] += e;
                     st[2] = fmaf(e, g[i], st[2]);
                 }
@@ -1060,7 +1102,7 @@ __device__ __forceinline__ void row_loop(const RowArgs &a, int c, int grp, const
                 decode<DT>(t0, q, 1.f);
                 decode<DT>(t1, g, gs);
                 for (int i = 0; i < tn; ++i) {
-                    const float e = fast_exp2(fmaf(ref.less(q[i]), K, nct));
+                    const float e = fast_exp2(fmaf(q[i], K, nct));
                     st[1] += e;
                     st[2] = fmaf(e, g[i], st[2]);
                 }
@@ -1074,7 +1116,7 @@ __device__ __forceinline__ void row_loop(const RowArgs &a, int c, int grp, const
                 decode<DT>(xv, q, 1.f);
                 decode<DT>(gv, g, gs);
 #pragma unroll
-                for (int i = 0; i < EPV; ++i) dx[i] = fast_exp2(fmaf(ref.less(q[i]), K, csh)) * invs_s * (g[i] - cdot);
+                for (int i = 0; i < EPV; ++i) dx[i] = fast_exp2(fmaf(q[i], K, csh)) * invs_s * (g[i] - cdot);
             };
             float oinv = 1.f;
             if constexpr (FP8) {

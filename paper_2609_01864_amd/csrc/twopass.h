@@ -94,6 +94,55 @@ __device__ __forceinline__ void code_store(char *row, int64_t v, int nv, const u
     for (int i = 0; i < nv; ++i) p[i] = (char)((w[i / 4] >> (8 * (i % 4))) & 0xffu);
 }
 
+// The softmax of a far row (device.h), or its backward from the logits, in three
+// passes: its maximum, the sums about it, the output.  `max1` and `sum2` reduce
+// over the workgroup.  (Threads of a row that is not far skip vectors that are: they
+// add nothing.  What a far row left in the one pass that the others need is not
+// used.)  Rare, so short: it must not cost the loops beside it registers.
+template <bool BWD, int DT, int BLOCK, class Max, class Sum>
+__device__ __forceinline__ void far_softmax_row(const char *r0, const char *r1, char *orow, int64_t N, int flags, Max max1,
+                                                Sum sum2) {
+    constexpr int EPV = Io<DT>::EPV;
+    auto each = [&](auto f) {
+        int64_t e = (int64_t)threadIdx.x * EPV;
+        asm volatile("" : "+v"(e));  // else what follows from it is kept through the row loop
+#pragma nounroll
+        for (; e < N; e += (int64_t)BLOCK * EPV) {
+            const int nv = N - e < EPV ? (int)(N - e) : EPV;
+            float q[EPV], g[EPV];
+            decode<DT>(load_vec<DT, false>(r0, e, nv, flags & F_ALIGN0), q, 1.f);
+            if constexpr (BWD) decode<DT>(load_vec<DT, false>(r1, e, nv, flags & F_ALIGN1), g, 1.f);
+            f(e, nv, q, g);
+        }
+    };
+    float m[1] = {-INFINITY};
+    each([&](int64_t, int nv, float (&q)[EPV], float (&)[EPV]) {
+#pragma unroll
+        for (int i = 0; i < EPV; ++i) m[0] = fmaxf(m[0], i < nv ? q[i] : -INFINITY);
+    });
+    max1(m);
+    float st[2] = {0.f, 0.f};
+    each([&](int64_t, int nv, float (&q)[EPV], float (&g)[EPV]) {
+#pragma unroll
+        for (int i = 0; i < EPV; ++i) {
+            const float x = i < nv ? fast_exp2((q[i] - m[0]) * kLog2e) : 0.f;
+            st[0] += x;
+            if constexpr (BWD) st[1] = fmaf(x, g[i], st[1]);
+        }
+    });
+    sum2(st);
+    const float inv = 1.f / st[0], dot = st[1] * inv;
+    each([&](int64_t e, int nv, float (&q)[EPV], float (&g)[EPV]) {
+        float y[EPV];
+#pragma unroll
+        for (int i = 0; i < EPV; ++i) {
+            y[i] = fast_exp2((q[i] - m[0]) * kLog2e) * inv;
+            if constexpr (BWD) y[i] *= g[i] - dot;
+        }
+        store_vec<DT>(orow, e, nv, flags & F_ALIGNO, encode<DT>(y, 1.f));
+    });
+}
+
 template <int OP, int DT, int BLOCK, int U>
 __global__ __launch_bounds__(BLOCK) void k_twopass(RowArgs a) {
     constexpr int EPV = Io<DT>::EPV, B = Io<DT>::BYTES, NW = BLOCK / 64;
@@ -115,7 +164,6 @@ __global__ __launch_bounds__(BLOCK) void k_twopass(RowArgs a) {
         if constexpr (OP == OP_SOFTMAX_FWD) {
             const float K = (FP8 ? a.s0[row] : 1.f) * kLog2e;
             float st[2] = {-INFINITY, 0.f};  // online base-2 (c, s)
-            float qm = -INFINITY;            // the largest logit so far, of reference c
             stream_row<DT, BLOCK, U, false>(r0, nullptr, N, al0, al1, [&](int64_t, u32x4 v, u32x4, int nv) {
                 float q[EPV];
                 decode<DT>(v, q, 1.f);
@@ -123,30 +171,36 @@ __global__ __launch_bounds__(BLOCK) void k_twopass(RowArgs a) {
 #pragma unroll
                 for (int i = 0; i < EPV; ++i)
                     if (i < nv) bm = fmaxf(bm, q[i]);
-                if (bm == -INFINITY) return;
-                const float cb = base2_ref(bm, K);
-                if (cb > st[0] || (cb == st[0] && bm > qm)) {
-                    qm = bm;
+                const float cb = bm * K;
+                if (FP8 ? bm == -INFINITY : cb <= -kFar) return;
+                if (cb > st[0]) {
                     st[1] = st[0] == -INFINITY ? 0.f : st[1] * fast_exp2(st[0] - cb);
                     st[0] = cb;
                 }
-                const FarRef<FP8> ref(st[0], qm);
 #pragma unroll
                 for (int i = 0; i < EPV; ++i)
-                    if (i < nv) st[1] += fast_exp2(fmaf(ref.less(q[i]), K, ref.about()));
+                    if (i < nv) st[1] += fast_exp2(fmaf(q[i], K, -st[0]));
             });
-            const FarRef<FP8> ref(st[0], qm);
             block_reduce<NW, 2>(st, MergeSoftmax(), red, parity);
-            const float cmax = st[0], inv_s = 1.f / st[1];
+            const float cmax = st[0];
+            if constexpr (!FP8) {
+                if (__builtin_expect(far_ref(cmax) || cmax == -INFINITY, 0)) {
+                    far_softmax_row<false, DT, BLOCK>(
+                        r0, r1, orow, N, a.flags, [&](float (&v)[1]) { block_reduce<NW, 1>(v, MergeMax(), red, parity); },
+                        [&](float (&v)[2]) { block_reduce<NW, 2>(v, MergeSum(), red, parity); });
+                    continue;
+                }
+            }
+            const float inv_s = 1.f / st[1];
             const float omul = FP8 ? kFp8Max : inv_s;
-            const float csh = ref.out(kExpShift, cmax), omuls = omul * kExpUnshift;
+            const float csh = kExpShift - cmax, omuls = omul * kExpUnshift;
             if (FP8 && writer) a.so[row] = inv_s / kFp8Max;
             stream_row<DT, BLOCK, U, true>(r0, nullptr, N, al0, al1, [&](int64_t v, u32x4 d, u32x4, int nv) {
                 if (nv == 0) return;
                 float q[EPV], y[EPV];
                 decode<DT>(d, q, 1.f);
 #pragma unroll
-                for (int i = 0; i < EPV; ++i) y[i] = fast_exp2(fmaf(ref.less(q[i]), K, csh)) * omuls;
+                for (int i = 0; i < EPV; ++i) y[i] = fast_exp2(fmaf(q[i], K, csh)) * omuls;
                 row_store<DT>(orow, v, nv, encode<DT>(y, 1.f));
             });
         } else if constexpr (OP == OP_LN_FWD || OP == OP_RMS_FWD || OP == OP_LN_BWD || OP == OP_RMS_BWD ||
@@ -321,7 +375,6 @@ __global__ __launch_bounds__(BLOCK) void k_twopass(RowArgs a) {
             // streams them again
             const float K = (FP8 ? a.s0[row] : 1.f) * kLog2e, gs = FP8 ? a.s1[row] : 1.f;
             float st[3] = {-INFINITY, 0.f, 0.f};
-            float qm = -INFINITY;  // the largest logit so far, of reference c
             stream_row<DT, BLOCK, U, false>(r0, r1, N, al0, al1, [&](int64_t, u32x4 xv, u32x4 gv, int nv) {
                 float q[EPV], g[EPV];
                 decode<DT>(xv, q, 1.f);
@@ -330,35 +383,41 @@ __global__ __launch_bounds__(BLOCK) void k_twopass(RowArgs a) {
 #pragma unroll
                 for (int i = 0; i < EPV; ++i)
                     if (i < nv) bm = fmaxf(bm, q[i]);
-                if (bm == -INFINITY) return;
-                const float cb = base2_ref(bm, K);
-                if (cb > st[0] || (cb == st[0] && bm > qm)) {
-                    qm = bm;
+                const float cb = bm * K;
+                if (FP8 ? bm == -INFINITY : cb <= -kFar) return;
+                if (cb > st[0]) {
                     const float f = st[0] == -INFINITY ? 0.f : fast_exp2(st[0] - cb);
                     st[1] *= f;
                     st[2] *= f;
                     st[0] = cb;
                 }
-                const FarRef<FP8> ref(st[0], qm);
 #pragma unroll
                 for (int i = 0; i < EPV; ++i) {
                     if (i < nv) {
-                        const float e = fast_exp2(fmaf(ref.less(q[i]), K, ref.about()));
+                        const float e = fast_exp2(fmaf(q[i], K, -st[0]));
                         st[1] += e;
                         st[2] = fmaf(e, g[i], st[2]);
                     }
                 }
             });
-            const FarRef<FP8> ref(st[0], qm);
             block_reduce<NW, 3>(st, MergeSoftmax3(), red, parity);
-            const float cmax = st[0], inv_s = 1.f / st[1], cdot = st[2] * inv_s;
-            const float csh = ref.out(kExpShift, cmax), invs_s = inv_s * kExpUnshift;
+            const float cmax = st[0];
+            if constexpr (!FP8) {
+                if (__builtin_expect(far_ref(cmax) || cmax == -INFINITY, 0)) {
+                    far_softmax_row<true, DT, BLOCK>(
+                        r0, r1, orow, N, a.flags, [&](float (&v)[1]) { block_reduce<NW, 1>(v, MergeMax(), red, parity); },
+                        [&](float (&v)[2]) { block_reduce<NW, 2>(v, MergeSum(), red, parity); });
+                    continue;
+                }
+            }
+            const float inv_s = 1.f / st[1], cdot = st[2] * inv_s;
+            const float csh = kExpShift - cmax, invs_s = inv_s * kExpUnshift;
             auto h = [&](u32x4 xv, u32x4 gv, float *dx) {
                 float q[EPV], g[EPV];
                 decode<DT>(xv, q, 1.f);
                 decode<DT>(gv, g, gs);
 #pragma unroll
-                for (int i = 0; i < EPV; ++i) dx[i] = fast_exp2(fmaf(ref.less(q[i]), K, csh)) * invs_s * (g[i] - cdot);
+                for (int i = 0; i < EPV; ++i) dx[i] = fast_exp2(fmaf(q[i], K, csh)) * invs_s * (g[i] - cdot);
             };
             float oinv = 1.f;
             if constexpr (FP8) {
