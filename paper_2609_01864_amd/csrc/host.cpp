@@ -452,7 +452,9 @@ const void *stream_fn(int k_op, int dt, int v, int r, bool split, bool full) {
 // v == 0: the one-row kernel is kept.
 struct StreamForm {
     int v = 0, r = 0, cap = 0;
-    bool many = false;  // only for more than two rounds (row-resident), five (split)
+    int more = 0;  // only for more rounds than these (0: resolve_stream's own least)
+    int rows = 0;  // row-resident: only for more rows per CU than these,
+    int most = 0;  // and up to these (0: any); split: up to these rounds as well
 };
 
 // LayerNorm / RMSNorm backward, back to back on MI355X (us, one-row kernel ->
@@ -492,7 +494,11 @@ StreamForm stream_form_norm_bwd(int k_op, int dt, int k, int64_t cvec) {
 // 31.5, ragged 8192 x 3001 36 -> 22, FP32 4095 x 5003 44 -> 33 and 37.5 -> 33; 4096 x
 // 16384 BF16 53 -> 49 and 50 -> 46, FP32 98 -> 94.  Two rounds of long rows are too
 // few to pay for the longer start unless the one-row kernel's rows are ragged
-// (FP32 1024 x 8192 9.9 against 12.0; 256 x 16385 BF16 12.2 -> 9.2).  Split: BF16 2048
+// (FP32 1024 x 8192 9.9 against 12.0; 256 x 16385 BF16 12.2 -> 9.2), and up to 6 rows per
+// CU BF16 ones of 129 to 256 vectors, 4 a round, leave half the CUs one workgroup of two
+// waves (LayerNorm 1250 x 1280 8.3 against 9.5, RMSNorm 7.4 against 8.4, 1600 rows even;
+// ragged 1250 x 1300 9.1 -> 8.2); so do FP32 RMSNorm ones of 1024 (520 x 4096 7.5 against
+// 8.8).  Split: BF16 2048
 // x 131072 k = 8 238 -> 198 (LayerNorm), 198 -> 181, k = 16 244 -> 221 and 195 -> 196;
 // ragged 2048 x 100001 k = 8 282 -> 200 and 242 -> 170; 4096 x 16384 k = 8 166 -> 57.
 // FP32 slices over 1024 vectors win only with few members (1024 x 131072 k = 8 190
@@ -508,10 +514,10 @@ StreamForm stream_form_norm_bwd(int k_op, int dt, int k, int64_t cvec) {
 StreamForm stream_form_norm_fwd(int k_op, int dt, int k, int64_t cvec, bool whole, bool aligned) {
     const bool ln = k_op == OP_LN_FWD, f32 = dt == CREDIT_F32;
     if (k == 1) {
-        if (cvec <= 256 && !f32) return {2, 4, 0};
-        if (cvec <= 1024) return {2, 2, 0};
-        if (cvec <= 2048) return {4, 1, 0, aligned};
-        if (cvec <= 4096) return {8, 1, 0, aligned};
+        if (cvec <= 256 && !f32) return {2, 4, 0, 0, cvec > 128 && aligned ? 6 : 0};
+        if (cvec <= 1024) return {2, 2, 0, 0, f32 && !ln && cvec > 960 ? 3 : 0};
+        if (cvec <= 2048) return {4, 1, 0, aligned ? 2 : 0};
+        if (cvec <= 4096) return {8, 1, 0, aligned ? 2 : 0};
         return {};
     }
     if (cvec <= 128 || (cvec <= 256 && (f32 || !ln))) return {1, 4, 0};
@@ -521,11 +527,11 @@ StreamForm stream_form_norm_fwd(int k_op, int dt, int k, int64_t cvec, bool whol
         if (cvec <= 1024) return ln ? StreamForm{2, 2, 0} : StreamForm{2, 4, 0};
         if (cvec <= 2048 && k <= 4) {
             if (cvec <= (ln ? 1280 : 1536) || (ln && whole && cvec < 2048)) return {};
-            return {4, 1, 0, whole};
+            return {4, 1, 0, whole ? 5 : 0};
         }
         if (k < 4 || k > 8 || cvec > 4096 || cvec <= (ln ? 1280 : 1792)) return {};
         if (cvec > 2048 && cvec <= (ln ? 3072 : 2816)) return {};
-        return {8, 1, 0, whole && (!ln || cvec > 2048)};
+        return {8, 1, 0, whole && (!ln || cvec > 2048) ? 5 : 0};
     }
     if (cvec <= 512) return {2, 2, 0};
     if (cvec <= 1024) return whole && !ln ? StreamForm{2, 4, 0} : StreamForm{2, 2, 0};
@@ -539,34 +545,76 @@ StreamForm stream_form_norm_fwd(int k_op, int dt, int k, int64_t cvec, bool whol
 // 22, FP32 33.5 -> 26; 8192 x 3000 BF16 29.6 -> 22.8; 4096 x 16385 70 -> 62 and 122 ->
 // 86; 2048 x 50257 forward 107 -> 82 (98 with the vectors counted from the row's
 // start).  Split: 2048 x 50257 k = 2 111 -> 93 and 184 -> 130, k = 4 106 -> 91 and 173
-// -> 132, FP32 forward k = 4 154 -> 145; 8192 x 3000 k = 2 55 -> 36 and 66 -> 43. Slices
-// over 512 vectors keep the one-row kernels where rows are whole lines (2048 x
-// 32768 k = 2 51.7 against 53.6 and 76 against 80; 1431 x 71488 k = 2 89 against 106), as do
-// FP32 ones of the backward (2048 x 50257 k = 8 224 against 232) and slices of 9 waves
-// (900 rows of 4400 vectors k = 2 70.2 against 74.1; 6100 88.3 -> 82.4).  Resident BF16 rows
-// of one workgroup per CU take more than two rounds (400 x 64800 23.1 against 25.2, 900
-// rows 53.3 -> 49.8).
+// -> 132; 8192 x 3000 k = 2 55 -> 36 and 66 -> 43.  Resident BF16 rows of one workgroup
+// per CU take more than two rounds (400 x 64800 23.1 against 25.2, 900 rows 53.3 ->
+// 49.8).
+//
+// The line of a rule is where the one-row kernel's loads are as wide as these -- rows
+// of whole vectors (`aligned`) or, less so, of whole words -- and the slice's waves
+// fill the CU's 16 badly, as 5 to 7 and 9 to 12 do, or there are too few rounds for the
+// loads of the next one to matter.  Row-resident, aligned: BF16 forward of 6 waves up
+// to 8 rows per CU (1100 x 10624 17.2 -> 16.3; 3000 x 10496 30.5 against 35.5), of 9 and 10
+// never (4600 x 16576 64.6 against 71.2), of 129 to 256 vectors over 4 rows per CU (600 x
+// 1152 7.0 against 7.9, 2048 rows 10.0 -> 8.6); backward over 8 rows per CU (BF16 1700 x
+// 10752 27.2 against 31.4, FP32 600 x 4864 11.5 against 13.0, 4600 50.6 -> 48.4), BF16 of
+// 513 to 1024 vectors never (4600 x 4816 33.1 against 37.6).  Split, forward: slices over
+// 512 vectors keep the one-row kernels where rows are whole lines (2048 x 32768 k = 2 51.7
+// against 53.6 and 76 against 80; 1431 x 71488 k = 2 89 against 106), BF16 ones of even
+// rows up to 12 waves (2493 x 66826 k = 4, 9 waves, 151 against 188; 844 x 30320 k = 2, 8,
+// 27.6 against 34.3; 332 x 56774 k = 2, 14, 37.6 -> 27.9), of odd rows at 6, 9 and 10 waves
+// (6144 x 29895 k = 2, 8 waves, 184 -> 152), FP32 ones up to 6 rounds and more (576 x 24642 k =
+// 2, 13 waves, 31.1 against 37.3, 3072 x 26338 130 -> 123).  Split, backward: FP32 over 512
+// vectors never (2048 x 50257 k = 8 224 against 232), BF16 of aligned rows over 8 rounds
+// (332 x 51800 k = 2 32.5 against 36.7, 3072 x 54320 236 -> 202), of 4 and 5 waves never
+// (211 x 75016 k = 8 34.8 against 45.6); odd rows gain everywhere (768 x 208199 k = 8 301 ->
+// 203).
 //
 // FP8 (forward): 4 vectors a lane, their exponentials kept, so that each is taken
 // once, where slices are whole vectors of every lane (4096 x 65536 113 -> 95, 1024 x
 // 262144 k = 4 122 -> 108) and for resident rows that end in a part of a vector (4096
 // x 17001 61 -> 51); the others gain nothing (2000 x 30000 31.9 against 31.2, 1500 x
 // 16400 20.4 against 22.6, 1500 x 100001 k = 4 96.4 against 99.9), nor do 9 to 12 waves,
-// one workgroup per CU (3000 x 33333 67.9 against 69.6).
+// one workgroup per CU (3000 x 33333 67.9 against 69.6), and up to 6 rows per CU one or
+// two waves whose tail is an element or two, which the one-row kernel takes in its
+// stride (450 x 1441 8.9 against 10.4).
 StreamForm stream_form_softmax(int k_op, int dt, int k, int64_t cvec, int64_t N) {
-    const bool fwd = k_op == OP_SOFTMAX_FWD, lines = N % (8 * dt_epv(dt)) == 0;
+    const bool fwd = k_op == OP_SOFTMAX_FWD, f32 = dt == CREDIT_F32;
+    const bool lines = N % (8 * dt_epv(dt)) == 0, aligned = N % dt_epv(dt) == 0;
+    const int64_t c = cvec + 9;  // up to 8 vectors more than the slice's (stream_softmax.h)
     if (dt == CREDIT_FP8_E4M3) {
-        const bool whole = N == k * cvec * 16 && cvec % 256 == 0;
-        return cvec <= 4096 && (whole || (k == 1 && N % 16 && cvec + 9 <= 4096 && (cvec + 9 <= 2048 || cvec > 3072))) ? StreamForm{4, 1, 0} : StreamForm{};
+        if (N == k * cvec * 16 && cvec % 256 == 0) return cvec <= 4096 ? StreamForm{4, 1, 0} : StreamForm{};
+        if (k > 1 || N % 16 == 0 || c > 4096 || (c > 2048 && cvec <= 3072)) return {};
+        return {4, 1, 0, 0, c <= 512 && N % 16 <= 2 ? 6 : 0};
     }
-    if (cvec <= (fwd || k == 1 ? 64 : 640)) return {1, 2, 0};
-    if (cvec <= 512) return {2, 2, 0};
-    if (k > 1 && (lines || (dt == CREDIT_F32 && !fwd))) return {};
-    // up to 8 vectors more than the slice's (stream_softmax.h)
-    if (cvec + 9 <= 4096) return {4, 1, 0};
-    if (k > 1 && cvec + 9 <= 4608) return {};
-    if (fwd && cvec + 9 <= 8192) return {8, 1, 0, k == 1 && dt != CREDIT_F32 && cvec + 9 > 6144};
-    return {};
+    // least rows per CU of a row-resident plan
+    const int rows = fwd        ? (!f32 && aligned && cvec > 128 && cvec <= 256 ? 4 : 0)
+                   : !aligned   ? (f32 && cvec > 1024 && cvec <= 1536 ? 4 : 0)
+                   : cvec <= 128 || cvec > 3072 ? 0
+                   : cvec <= 256 || (f32 && cvec > 512 && cvec <= 1024) ? 4 : cvec <= 2048 ? 8 : 6;
+    const bool mid = k > 1 && !fwd && !f32 && aligned && cvec > 512 && cvec <= 768;
+    if (cvec <= (fwd || k == 1 ? 64 : 640)) return {1, 2, 0, mid ? 6 : 0, rows};
+    if (cvec <= 512) return {2, 2, 0, 0, rows};
+    if (k == 1) {
+        if (c > 4096) return fwd && c <= 8192 ? StreamForm{8, 1, 0, !f32 && c > 6144 ? 2 : 0} : StreamForm{};
+        const bool six = !f32 && aligned && c > 1280 && c <= 1536;  // waves
+        if (!f32 && aligned && (fwd ? c > 2048 && c <= 2560 : cvec <= 1024)) return {};
+        return {4, 1, 0, 0, rows, !six ? 0 : fwd ? 8 : 20};
+    }
+    if (lines || (f32 && !fwd) || (c > 4096 && c <= 4608)) return {};
+    if (c > 4096) return fwd && c <= 8192 ? StreamForm{8, 1, 0} : StreamForm{};
+    if (f32) {
+        if (c <= 1024) return {4, 1, 0};
+        if (c <= 1536) return {4, 1, 0, 8};
+        if (c <= 1792 || (c > 2048 && c <= 2304)) return {};
+        return {4, 1, 0, 6, 0, c > 3584 ? 3 : 0};
+    }
+    if (!fwd) {
+        if ((aligned && cvec > 768 && cvec <= 1280) || (N % 2 == 0 && c > 1024 && c <= 1280)) return {};
+        return {4, 1, 0, mid ? 6 : aligned ? 8 : N % 2 || c > 2048 ? 0 : 3};
+    }
+    if (N % 2 == 0 && c > (aligned ? 768 : 1024) && c <= 3072) return {};
+    if (N % 2 && ((c > 1280 && c <= 1536) || (c > 2048 && c <= 2560))) return {};
+    return {4, 1, 0};
 }
 
 // Row-wise int8 quantisation (stream_quant.h), as above (us, inputs from HBM): BF16
@@ -639,8 +687,12 @@ void resolve_stream(credit_handle_t h, int k_op, int dt, int64_t M, int64_t N, L
     const int64_t blocks = (M + f.r - 1) / f.r;
     if (gmax < 1) return;
     const bool bwd = k_op == OP_LN_BWD || k_op == OP_RMS_BWD;
-    if (L.k > 1 ? blocks < gmax || (!bwd && blocks <= (f.many ? 5 : f8 ? 3 : 2) * gmax)
-                : blocks < std::min<int64_t>(gmax, h->cus) || (f.many && blocks <= 2 * gmax))
+    const int64_t cus = std::min<int64_t>(gmax, h->cus);
+    const int least = L.k == 1 || bwd ? 0 : f8 ? 3 : 2;
+    if (L.k > 1 ? blocks < gmax || blocks <= least * gmax ||
+                      (blocks <= f.more * gmax && (!f.most || blocks > f.most * gmax))
+                : blocks < cus || M <= f.rows * cus || (f.most && M > f.most * cus) ||
+                      (f.more && blocks <= f.more * gmax))
         return;
     int64_t groups = 0;
     if (L.k > 1) {
@@ -657,26 +709,27 @@ void resolve_stream(credit_handle_t h, int k_op, int dt, int64_t M, int64_t N, L
         // round more than others (FP8 softmax of 1165 rows, 5 waves each:
         // 583 groups of 2 rounds 22.9 us, 768 groups 19.1; FP32 LayerNorm 4095 x 5003, a tie: 31.8
         // against 34.5).
-        int64_t least = INT64_MAX;
+        int64_t fewest = INT64_MAX;
         for (int p = occ; p >= (occ + 1) / 2; --p) {
             const int64_t g = std::min<int64_t>(gmax, (int64_t)p * h->cus);
             const int64_t rounds = (blocks + g - 1) / g, n = (blocks + rounds - 1) / rounds;
             const int64_t busiest = (n + h->cus - 1) / h->cus * rounds;
-            if (busiest < least) {
-                least = busiest;
+            if (busiest < fewest) {
+                fewest = busiest;
                 groups = n;
             }
         }
         const int64_t all = std::min(gmax, blocks);
         int64_t busiest = 0;  // CU 0 has the first of every h->cus groups
         for (int64_t w = 0; w < all; w += h->cus) busiest += (blocks - w + all - 1) / all;
-        // A tie goes to as many as fit for FP8 softmax alone: its time is its
-        // instructions', and one workgroup of 6 to 8 waves per CU leaves half the
-        // SIMDs idle (1200 x 21535: 240 groups of 5 rounds 26.3 us, 512 groups 19.7; 2200 x
-        // 30001 44.4 against 34.5); the forms bound by memory lose (BF16 quantisation
-        // 2200 x 29001 37.9 with fewest, 43.3).
-        const bool tie = busiest == least && groups <= h->cus && f8 && k_op == OP_SOFTMAX_FWD;
-        if (!ncp_of(k_op) && (busiest < least || tie)) groups = all;
+        // FP8 softmax alone, whose time is its instructions', takes as many as fit up
+        // to 4 waves (two workgroups of 4 leave half of each SIMD's slots empty: 2500 x
+        // 12770 35.8 us in 512 groups of 5 rounds, 25.9 in 1024 of 3; of 5 waves, 2500 x
+        // 16866, 36.9 against 42.7), and at a tie (1200 x 21535: 240 groups of 5 rounds 26.3,
+        // 512 groups 19.7; 2200 x 30001 44.4 against 34.5); the forms bound by memory lose
+        // (BF16 quantisation 2200 x 29001 37.9 with fewest, 43.3).
+        const bool tie = f8 && k_op == OP_SOFTMAX_FWD && (w <= 4 || (busiest == fewest && groups <= h->cus));
+        if (!ncp_of(k_op) && (busiest < fewest || tie)) groups = all;
     }
     L.stream = true;
     L.chunk = cv * epv;
