@@ -1445,9 +1445,11 @@ int bytes_rank(int c) { return c == 0 ? CREDIT_NUM_PLANS : c; }
 // fewest members they need (BF16 LayerNorm backward 4096 x 5120: 34 us resident,
 // 46 at the network's k = 2; 4096 x 16384: 88 at k = 2 and 4, 91 at 8; forward 4096 x
 // 16384 FP32 93.8 resident, 95.8 at k = 2): the fixed rule's plan, if it streams.
-// Else the first plan that does, where the one-row kernels are slower at the
-// factors the network knows: LayerNorm backward up to k = 16 (FP32 898 x 32528 82 at
-// 8, 94 at the network's 4; 1000 x 50000 138 at 16, 150; 1024 x 131072 320 at 16, 327 at
+// Else, but for rows of up to 1024 vectors -- they stream row-resident unless they
+// are few, and are then better off as they were (LayerNorm backward BF16 823 x 512 12.7
+// resident, 25.5 at k = 16) --, the first plan that does, where the one-row kernels are
+// slower at the factors the network knows: LayerNorm backward up to k = 16 (FP32 898 x
+// 32528 82 at 8, 94 at the network's 4; 1000 x 50000 138 at 16, 150; 1024 x 131072 320 at 16, 327 at
 // 32), BF16 forward up to 8 (LayerNorm 2048 x 131072 196 at 8, 214 at the network's 4;
 // RMSNorm 2000 x 50000 86 at 2, 97), FP8 LayerNorm forward at any -- there the second
 // such plan where the first leaves one workgroup of 13 to 16 waves per CU, whose
@@ -1460,6 +1462,7 @@ bool stream_default(credit_handle_t h, int k_op, int dt, int64_t M, int64_t N, c
     const int most = f8 ? kMaxK
                    : k_op == OP_LN_BWD ? 16
                    : (k_op == OP_LN_FWD || k_op == OP_RMS_FWD) && dt == CREDIT_BF16 ? 8 : 0;
+    const bool few = !f8 && N <= 1024 * dt_epv(dt);
     bool found = false;
     for (int c = 1; c < CREDIT_NUM_PLANS; ++c) {
         const credit_plan_t p = class_plan(c);
@@ -1470,7 +1473,8 @@ bool stream_default(credit_handle_t h, int k_op, int dt, int64_t M, int64_t N, c
             if (found || !f8 || N < 32768 || L.block <= 768) return true;
             found = true;
         }
-        if (c + 1 < CREDIT_NUM_PLANS && class_plan(c + 1).k > most) break;  // (the first legal one is the fixed rule's)
+        // (the first legal one is the fixed rule's)
+        if (c + 1 < CREDIT_NUM_PLANS && (class_plan(c + 1).k > most || few)) break;
     }
     return found;
 }

@@ -54,3 +54,22 @@ def test_default_plan_follows_the_rows_option(lib_built, monkeypatch, tmp_path):
         fresh.close()
     plans = [json.loads(line)["plan"] for line in path.read_text().splitlines()]
     assert plans[0] != plans[1] and plans[1] == plans[2] and plans[3] == plans[0]
+
+
+def test_default_plan_of_few_short_rows_is_the_networks(lib_built, monkeypatch, tmp_path):
+    # too few rows to stream row-resident: not a reason to split short rows
+    # (LayerNorm backward 823 x 512 BF16: 12.7 us resident, 25.5 at k = 16)
+    path = tmp_path / "calls.jsonl"
+    monkeypatch.setenv("CREDIT_LOG", str(path))
+    x, dy = (torch.randn((823, 512), device="cuda").bfloat16() for _ in range(2))
+    g = torch.rand(512, device="cuda")
+    h = C.Handle(0)
+    try:
+        print("[default plan] few short rows", flush=True)
+        C.layernorm_bwd(x, dy, g, None, None, h=h)
+        torch.cuda.synchronize()
+        f = h.mlp_predict(C.features(C.LAYERNORM, C.BWD, C.BF16, 823, 512)[None, :])[0]
+    finally:
+        h.close()
+    used = json.loads(path.read_text().splitlines()[-1])["plan"]
+    assert used == [1, 1] and f.argmax() == 1
