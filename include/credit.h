@@ -49,8 +49,11 @@
  *     fills the cache with the configured selector's choice, timing kernels
  *     where that selector times), else the learned network's first legal
  *     choice, computed on the handle's stream in buffers allocated when the
- *     model was set (the fixed rule without a model, and for the LayerNorm /
- *     RMSNorm backward where the fixed rule's plan runs in the streaming form).
+ *     model was set (the fixed rule without a model) -- unless a plan that
+ *     runs in the streaming form is known to be better: the fixed rule's where
+ *     it streams, else the first that does for the FP8 LayerNorm forward and,
+ *     for rows of more than 1024 16-byte vectors, the LayerNorm backward (up to
+ *     16 members) and the BF16 LayerNorm / RMSNorm forward (up to 8).
  *   - Operator calls may be recorded into a HIP graph (stream capture) and
  *     replayed: a recorded split-row launch is preceded by a one-thread kernel
  *     that advances a device-side exchange epoch, so every replay is a new

@@ -30,7 +30,7 @@ __device__ __forceinline__ float fast_exp2(float v) { return __builtin_amdgcn_ex
 // there, so the shifted exponential cannot overflow; the factor's product is
 // exact).  The FP32 softmax forward (register slots) and the FP8 one on
 // slices of up to 64 values per thread reuse the sum pass's unshifted
-// exponentials about each thread's own maximum instead: an output whose
+// exponentials about the thread's (streaming: the wave's) own maximum: an output whose
 // exponential lies below 2^-126 of that maximum is 0, an absolute error
 // under 1.2e-38 (FP32) or far below an e4m3 step (FP8).
 constexpr float kExpShift = 32.f;

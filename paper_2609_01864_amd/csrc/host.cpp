@@ -647,7 +647,7 @@ StreamForm stream_form_quant(int dt, int k, int64_t cvec) {
 //
 // FP8 LayerNorm forward (stream_fp8.h): slices of up to 1024 vectors, one a
 // lane, 4 rows a round, at every split factor (us): 4096 x 16384 52.6 -> 32.4, 4096 x
-// 65536 k = 8 328 -> 137 (k = 2, whose slices are too long: 219), 1024 x 262144 k = 16
+// 65536 k = 8 328 -> 140 (k = 2, whose slices are too long: 219), 1024 x 262144 k = 16
 // 308 -> 151 (k = 8: 244), 2000 x 30000 k = 2 68 -> 47, 1500 x 100001 k = 16 306 -> 114;
 // split from more than three rounds on (1200 x 16400 k = 2, 2.3 rounds: 30.4 against
 // 29.5 resident).
@@ -1449,11 +1449,11 @@ int bytes_rank(int c) { return c == 0 ? CREDIT_NUM_PLANS : c; }
 // are few, and are then better off as they were (LayerNorm backward BF16 823 x 512 12.7
 // resident, 25.5 at k = 16) --, the first plan that does, where the one-row kernels are
 // slower at the factors the network knows: LayerNorm backward up to k = 16 (FP32 898 x
-// 32528 82 at 8, 94 at the network's 4; 1000 x 50000 138 at 16, 150; 1024 x 131072 320 at 16, 327 at
-// 32), BF16 forward up to 8 (LayerNorm 2048 x 131072 196 at 8, 214 at the network's 4;
-// RMSNorm 2000 x 50000 86 at 2, 97), FP8 LayerNorm forward at any -- there the second
+// 32528 82 at 8, 94 at the network's 4; 1000 x 50000 138 at 16, 150; 1024 x 131072 320
+// at 16, 327 at 32), BF16 forward up to 8 (LayerNorm 2048 x 131072 196 at 8, 214 at the
+// network's 4; RMSNorm 2000 x 50000 86 at 2, 97), FP8 LayerNorm forward at any -- there the second
 // such plan where the first leaves one workgroup of 13 to 16 waves per CU, whose
-// barriers nothing hides (4096 x 65536 143 at k = 4, 137 at 8; 1500 x 100001 126 at 8,
+// barriers nothing hides (4096 x 65536 146 at k = 4, 140 at 8; 1500 x 100001 126 at 8,
 // 114 at 16; 1024 x 262144 151 at 16, 146 at 32; shorter rows would gain nothing: 2000 x
 // 30000 47 at 2, 49.5 at 4).
 bool stream_default(credit_handle_t h, int k_op, int dt, int64_t M, int64_t N, credit_plan_t *out) {

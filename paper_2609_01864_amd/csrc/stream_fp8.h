@@ -5,7 +5,7 @@
 // traffic and took 2.6 times as long as the latter (220 us for 83).  Here a lane
 // holds one vector (16 elements) of a slice with its gamma / beta in registers
 // for all its rows, a round is 4 rows, and later rounds' loads are in flight:
-// 137 us with k = 8.
+// 140 us with k = 8.
 //
 // The statistics (mean and M2, then the largest output) of the rows are reduced
 // for 4 rows at once: a wave folds its 4 registers into one, lane group ri (16
@@ -17,7 +17,7 @@
 // = 4, 118 without waiting for the polls; 1024 x 262144 k
 // = 16 166 -> 151).
 //
-// Bound: arithmetic, 12 instructions an element (90 of the 137 us: the output is
+// Bound: arithmetic, 12 instructions an element (90 of the 140 us: the output is
 // evaluated once for its maximum and once to be written), and the next rows'
 // loads, which have registers only from the moment the rows before are written.
 // More does not fit: the outputs kept between the two take 64 registers of the
