@@ -45,8 +45,8 @@ constexpr float kExpUnshift = 0x1p-32f;
 // neighbouring FP32 numbers may have the same c, and then count alike.)  A two-pass
 // row that is far is done over, in three passes.  FP8 codes do not reach it.  Other
 // rows pay for the test alone: 0 to 2% at the sizes where each kernel is the fastest;
-// short rows under an explicit two-pass plan, which no rule gives them, up to 40%
-// (FP32 12762 x 1579 52 -> 68 us, one-row 33; BF16 8979 x 940 34 -> 45).
+// many short rows under an explicit two-pass plan, which no rule gives them, 10%
+// (FP32 12762 x 1579 52 -> 57 us, one-row 33; BF16 8979 x 940 34 -> 37).
 constexpr float kFar = 0x1p29f, kFltMax = 0x1.fffffep+127f;
 __device__ __forceinline__ bool far_ref(float c) { return fabsf(c) >= kFar; }
 __device__ __forceinline__ float base2_ref(float qmax, float K) {

@@ -44,3 +44,10 @@ def test_fp8_softmax_fills_the_simds(gpu_handle):
     geo = gpu_handle.geometry(*s, C.plan("resident"))
     cus = torch.cuda.get_device_properties(0).multi_processor_count
     assert geo["block"] == 256 and geo["grid"] == geo["per_cu"] * cus
+
+
+def test_two_pass_softmax_grid_is_what_the_device_holds(gpu_handle):
+    # an eighth workgroup per CU would run after the others: 45 us, not 37
+    geo = gpu_handle.geometry(C.SOFTMAX, C.FWD, C.BF16, 8979, 940, C.plan("two_pass"))
+    cus = torch.cuda.get_device_properties(0).multi_processor_count
+    assert geo["grid"] <= 7 * cus
